@@ -40,7 +40,7 @@ PEAK_FP64_TFLOPS = 78.6
 # the kernel sources the counters were taken on (SHA-256 of their code
 # without comments and whitespace: the kernel template and launch shape, its
 # FP32 instantiation and the device headers it includes); otherwise null.
-KERNEL_SOURCES = ["sample_kernel.h", "single_f32.hip", "mcv_point.h", "mcv_device.h"]
+KERNEL_SOURCES = ["sample_kernel.h", "single.hip", "mcv_mask.h", "mcv_point.h", "mcv_device.h"]
 # Taken on d=10 / 32 channels / 100 bins, FP32 mode, 1e8 calls per launch
 # (profiles/k_sample_fp32_d10_K32_n100_counters.md).
 COUNTERS = {"sha256": "37043441b91977b1a4c0a79955d01bd417ffe0ddaa39c2d8095b69af0af32e25",

@@ -18,14 +18,17 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 ROOT = os.path.dirname(HERE)
 LIB = os.path.join(HERE, "libmcv.so")
-SOURCES = ["single_f64.hip", "single_f32.hip", "mrg_f64.hip", "mrg_f32.hip", "trace_f64.hip",
-           "trace_f32.hip", "sample.hip", "capi.hip", "jobs.hip", "batch.hip", "serve.hip",
-           "adapt.hip", "noalloc.hip", "strat.hip"]
+SOURCES = ["strat.hip", "sample.hip", "capi.hip", "jobs.hip", "batch.hip", "serve.hip",
+           "adapt.hip", "noalloc.hip"]
 ARCH = "gfx950"
 # per-source flags on top of common_flags()
 EXTRA_FLAGS = {"adapt.hip": ["-ffp-contract=off"]}
 # The batched sample kernel (queue.hip) is compiled once per precision, launch
 # bound and term-bound option, so that its variants compile in parallel.
+# So is the single-job sample kernel (single.hip): once per precision,
+# dimension bucket and generator.
+SINGLE_VARIANTS = [(prec, d, rng) for d in (32, 16, 12, 10, 8, 6, 4, 2) for prec in ("f64", "f32")
+                   for rng in (0, 1)]
 QUEUE_VARIANTS = [(prec, lb, tb) for prec in ("f32", "f64") for lb in (256, 512, 1024)
                   for tb in (1, 0)]
 
@@ -35,6 +38,9 @@ def units():
     out = [(f"queue_{p}_{lb}_{tb}.o", "queue.hip",
             [f"-DMCV_QUEUE_FP32={1 if p == 'f32' else 0}", f"-DMCV_QUEUE_LB={lb}",
              f"-DMCV_QUEUE_TB={tb}"]) for p, lb, tb in QUEUE_VARIANTS]
+    out += [(f"single_{p}_{d}_{r}.o", "single.hip",
+             [f"-DMCV_SINGLE_FP32={1 if p == 'f32' else 0}", f"-DMCV_SINGLE_D={d}",
+              f"-DMCV_SINGLE_RNG={r}"]) for p, d, r in SINGLE_VARIANTS]
     # the slowest objects first, so that the pool never waits on one at the end
     out += [(src.replace(".hip", ".o"), src, EXTRA_FLAGS.get(src, [])) for src in SOURCES]
     return out

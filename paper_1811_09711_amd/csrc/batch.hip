@@ -143,6 +143,7 @@ mcv_status Engine::build_set(const std::vector<int>& listed) {
     poff += (partial_bytes(j, G) + 255) & ~(size_t)255;
     const int b = sample_queue_layout(j, tune.block, host.data() + off_args + (size_t)i * abytes);
     if (b > lds) lds = b;
+    js.max_chunks = std::max(js.max_chunks, finalize_chunks(G, j.K));
     set_jobs.push_back(j);
   }
   memcpy(host.data() + off_table, set_jobs.data(), (size_t)n * sizeof(JobDev));
@@ -178,11 +179,7 @@ mcv_status Engine::enqueue_iteration(uint32_t what, hipStream_t s, hipEvent_t af
   if (launch_sample_queue(js, s) < 1) return fail(MCV_E_DEVICE, "batched sample launch failed");
   if (after_sample) MCV_HIP(hipEventRecord(after_sample, s));
   launch_finalize(js, 0, s);
-  if (what & MCV_REFINE_GRID) {
-    launch_refine_grid(js, s);
-    launch_tables(js, s);
-  }
-  if (what & MCV_REFINE_ALPHA) launch_update_alpha(js, s);
+  launch_refine(js, (what & MCV_REFINE_GRID) != 0, (what & MCV_REFINE_ALPHA) != 0, s);
   MCV_HIP(hipGetLastError());
   return MCV_OK;
 }

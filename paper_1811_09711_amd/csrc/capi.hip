@@ -230,12 +230,12 @@ mcv_status mcv_sample_iteration(mcv_integrator* h, int64_t n_points) {
   const mcv::JobSet one = mcv::single_set(j);
   mcv::launch_allocate(one, n_points, false, h->stream);
   MCV_HIP(hipEventRecord(h->ev0[it], h->stream));
-  const int G = j.strat > 0 ? mcv::launch_sample_strat(j, n_points, h->stream)
-                            : mcv::launch_sample(one, n_points, h->stream);
-  if (G < 1) return fail(MCV_E_DEVICE, "the sample kernel could not get its LDS");
+  const mcv::Split sp = j.strat > 0 ? mcv::launch_sample_strat(j, n_points, h->stream)
+                                    : mcv::launch_sample(j, n_points, h->stream);
+  if (sp.G < 1) return fail(MCV_E_DEVICE, "the sample kernel could not get its LDS");
   MCV_HIP(hipEventRecord(h->ev1[it], h->stream));
-  h->pass_G[it] = G;
-  mcv::launch_finalize(one, G, h->stream);
+  h->pass_G[it] = sp.G;
+  mcv::launch_finalize(one, sp.U, h->stream);
   MCV_HIP(hipGetLastError());
   h->n_iter += 1;
   h->last_n = n_points;
@@ -249,14 +249,8 @@ mcv_status mcv_refine(mcv_integrator* h, uint32_t what) {
     return fail(MCV_E_INVALID, "unknown refine flags");
   if (h->n_iter == 0) return fail(MCV_E_STATE, "refine before the first pass");
   const mcv::JobSet one = mcv::single_set(h->j);
-  if (what & MCV_REFINE_GRID) {
-    mcv::launch_refine_grid(one, h->stream);
-    mcv::launch_tables(one, h->stream);
-  }
-  if (what & MCV_REFINE_ALPHA) {
-    mcv::launch_update_alpha(one, h->stream);
-    h->alloc_valid = false;
-  }
+  mcv::launch_refine(one, (what & MCV_REFINE_GRID) != 0, (what & MCV_REFINE_ALPHA) != 0, h->stream);
+  if (what & MCV_REFINE_ALPHA) h->alloc_valid = false;
   MCV_HIP(hipGetLastError());
   return MCV_OK;
 }
@@ -458,16 +452,11 @@ mcv_status mcv_debug_sample_trace(mcv_integrator* h, int64_t n_points, int64_t i
   MCV_HIP(hipMemcpyAsync(&ntot, j.t_start + j.K, sizeof(int64_t), hipMemcpyDeviceToHost, s));
   MCV_HIP(hipStreamSynchronize(s));
   if (first + count > ntot) return fail(MCV_E_INVALID, "trace range beyond the pass");
-  const int G = j.prec == 1 ? mcv::sample_grid_f32(j, n_points) : mcv::sample_grid_f64(j, n_points);
-  if (G < 1) return fail(MCV_E_DEVICE, "the sample kernel could not get its LDS");
-  if (G > j.gmax) return fail(MCV_E_DEVICE, "more work units than partial buffers");
   double* out = nullptr;
   hipError_t e = mcv::dev_alloc((void**)&out, (size_t)count * 3 * sizeof(double));
   if (e == hipSuccess) {
-    const int r = j.prec == 1
-                      ? mcv::launch_sample_trace_f32(j, G, (uint32_t)iteration, first, count, out, s)
-                      : mcv::launch_sample_trace_f64(j, G, (uint32_t)iteration, first, count, out, s);
-    e = r < 1 ? hipErrorLaunchFailure : hipGetLastError();
+    const mcv::Split sp = mcv::single_trace(j, n_points, (uint32_t)iteration, first, count, out, s);
+    e = sp.G < 1 ? hipErrorLaunchFailure : hipGetLastError();
   }
   if (e == hipSuccess)
     e = hipMemcpyAsync(fgw, out, (size_t)count * 3 * sizeof(double), hipMemcpyDeviceToHost, s);

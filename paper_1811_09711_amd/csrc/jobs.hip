@@ -16,6 +16,7 @@
 #include <vector>
 
 #include "mcv_host.h"
+#include "mcv_mask.h"
 
 namespace mcv {
 
@@ -59,11 +60,12 @@ void carve_inputs(JobDev& j, Carve& c) {
   c.take(j.twin_peak, K);
   c.take(j.orphans, P);
   c.take(j.iter_dev, 1);
+  c.take(j.ticket, 1);
+  c.take(j.self, 1);
 }
 
 void carve_state(JobDev& j, Carve& c) {
   const size_t d = j.d, K = j.K, n = j.n, P = j.P, tsz = j.prec == 1 ? 4 : 8;
-  c.take(j.self, 1);
   c.take(j.cmap64, K * d);
   c.take(j.cmap32, K * d);
   c.take(j.cnorm64, K);
@@ -73,8 +75,6 @@ void carve_state(JobDev& j, Carve& c) {
   c.take(j.pnorm64, P);
   c.take(j.pnorm32, P);
   c.take(j.ctype, K);
-  c.take(j.twin_pn64, K);
-  c.take(j.twin_pn32, K);
   c.take(j.edges, K * d * (n + 1));
   char* xt = nullptr;
   char* pt = nullptr;
@@ -85,20 +85,20 @@ void carve_state(JobDev& j, Carve& c) {
   char* ct = nullptr;
   c.take(ct, K * d * (size_t)j.M * 4 * tsz);
   j.ctab = ct;
-  char* gb = nullptr;
-  c.take(gb, K * tsz);
-  j.gbound = gb;
-  char* at = nullptr;
-  c.take(at, 3 * K * tsz);
-  j.aterm = at;
-  char* tat = nullptr;
-  c.take(tat, 3 * K * tsz);
-  j.t_aterm = tat;
-  char* ga = nullptr;
-  c.take(ga, K * d * 2 * tsz);
-  j.gab = ga;
+  c.take(j.axmax, K * d);
+  c.take(j.next, 8);
+  const size_t stride = j.prec == 1 ? chan_stride<float>(j.d) : chan_stride<double>(j.d);
+  c.take(j.crec, K * stride);
+  c.take(j.t_crec, K * stride);
   c.take(j.hab, K * d * 2);
-  c.take(j.skx, K * 2);
+  if (j.masked) {
+    const size_t Kp = (K + 31) & ~(size_t)31;
+    _Float16* mc = nullptr;
+    c.take(mc, Kp * 16 * mask_form_of(j.d).steps);
+    j.mco = mc;
+    c.take(j.moff, Kp * 2);
+    c.take(j.mthr, Kp);
+  }
   c.take(j.alpha, K);
   c.take(j.nc, K);
   c.take(j.start, K + 1);
@@ -114,6 +114,28 @@ void carve_state(JobDev& j, Carve& c) {
   c.take(j.chstats, K * kStatStride);
   c.take(j.history, (size_t)j.max_iter * kHistStride);
   c.take(j.mrg, j.rng ? (size_t)kMrgTables * kMrgEntry + (K + 1) * 6 : 0);
+}
+
+// Whether a job's passes leave channels out by masks and put sparse lookups
+// off (mcv_mask.h, sample_kernel.h): in FP32 from four axes and four channels
+// that the mask can bound on.  Below that the channels' peaks overlap and few
+// are left out (24 channels: d = 2 273 us a pass with them, 227 without; d = 3
+// the same; d = 7 405 and 412, d = 10 840 and 1010, d = 12 290 and 380); in
+// FP64 the 3-axis partial exponent does as well and the queue costs more
+// registers than it saves (d = 10: 2.28 ms with masks, 1.96 without).  Their
+// lookup queues have to fit the LDS besides what the pass needs.
+bool wants_masks(const mcv_problem* p, JobDev j) {
+  if (p->precision != MCV_FP32_MIXED || p->dim < 4) return false;
+  const MaskForm f = mask_form_of(p->dim);
+  j.masked = 1;
+  if (f.steps == 0 || sample_lds_bytes(j) > 160 * 1024) return false;
+  int ng = 0;
+  for (int c = 0; c < p->n_channels; ++c) {
+    int g = 0;
+    for (int k = 0; k < p->dim; ++k) g += p->chan_kind[(size_t)c * p->dim + k] == MCV_GAUSS;
+    ng += f.axes > 0 ? g > 0 : g == p->dim;
+  }
+  return ng >= 4;
 }
 
 // MRG32k3a jump tables and stream starts (layout: JobDev::mrg), from the
@@ -312,6 +334,7 @@ size_t job_block_bytes(const mcv_problem* p, int gmax) {
   j.max_iter = p->max_iterations;
   j.rng = p->rng;
   j.strat = p->strat;
+  j.masked = gmax > 0 && wants_masks(p, j);
   Carve m;
   carve_inputs(j, m);
   carve_state(j, m);
@@ -345,6 +368,7 @@ mcv_status job_create(const mcv_problem* p, int gmax, int64_t n_points, int n_cu
   j.n_points = n_points;
   j.rng = p->rng;
   j.strat = p->strat;
+  j.masked = gmax > 0 && wants_masks(p, j);
   if (sample_lds_bytes(j) > 160 * 1024)
     return fail(MCV_E_INVALID, "dim * n_bins too large for the LDS of one workgroup");
   const size_t d = j.d, K = j.K, P = j.P;
@@ -374,6 +398,8 @@ mcv_status job_create(const mcv_problem* p, int gmax, int64_t n_points, int n_cu
       if (!taken[i]) orphan.push_back((int32_t)i);
   }
   j.n_orphan = (int)orphan.size();
+  for (size_t c = 0; c < K; ++c)
+    if (twin[c] >= 0 && p->peak_weight[twin[c]] < 0.0) j.fpos = 0;
 
   // measure, allocate, carve
   Carve m;
@@ -411,11 +437,10 @@ mcv_status job_create(const mcv_problem* p, int gmax, int64_t n_points, int n_cu
   memcpy(h.twin_peak, twin.data(), K * sizeof(int32_t));
   if (!orphan.empty()) memcpy(h.orphans, orphan.data(), orphan.size() * sizeof(int32_t));
   *h.iter_dev = 0;
+  *h.ticket = 0;
+  memcpy(h.self, &j, sizeof(JobDev));
 
   e = hipMemcpyAsync(dev, stage.data(), staged, hipMemcpyHostToDevice, s);
-  if (e == hipSuccess) e = hipMemcpyAsync(j.self, &j, sizeof(JobDev), hipMemcpyHostToDevice, s);
-  if (e == hipSuccess)
-    e = hipMemsetAsync(j.history, 0, (size_t)j.max_iter * kHistStride * sizeof(double), s);
   std::vector<uint32_t> mrg_tab;
   if (e == hipSuccess && j.rng) {
     mrg_tab = mrg_host_tables(j.seed, j.K);

@@ -19,6 +19,16 @@ namespace mcv {
 inline int hint_cells_for_bins(int n) { return n > 64 ? 512 : 256; }
 inline int hint_cell_shift(int M) { return M == 512 ? 18 : 19; }
 
+// Read-only kernel inputs are read through the constant address space, so
+// that wave-uniform reads become scalar loads.
+template <typename T>
+using CP = const __attribute__((address_space(4))) T*;
+
+template <typename T>
+__device__ __forceinline__ CP<T> cp(const T* p) {
+  return (CP<T>)(p);
+}
+
 enum { FLAT = 0, GAUSS = 1, BW = 2 };
 
 constexpr uint32_t kTagUnweight = 0x80000000u;
@@ -205,6 +215,47 @@ struct ChanType {
   int32_t lin;
 };
 
+// The log hint map of a flat axis, the same for every channel: z = 510 (x -
+// 1/2).
+constexpr float kFlatA = 510.0f, kFlatB = -255.0f;
+
+// What the channel loop reads of one channel, in one record (stride
+// chan_stride(d) bytes, one base address; as six arrays their addresses were
+// spilled to vector lanes and read back, 36 lane reads per channel, and each
+// array's read was waited for by itself): the masks of its Gaussian and
+// Breit-Wigner axes; iso, lin (ChanType), and pair: no Gaussian axis and one
+// or two Breit-Wigner ones, the others flat; the offsets ea, eb of the FP64
+// skip from a partial exponent; its peak's factor of f (0: no peak of its
+// shape); and, written with the allocation, the term's factor (T)alpha_c
+// cnorm_c, the term bound's factor (T)alpha_c gbound_c, and alpha_c cnorm_c
+// 2^s (1 + m) rounded up (the factor of the bound from looked-up densities).
+// The 2d density-kernel constants of
+// the axes follow: (ga, gb) on a Gaussian axis, (m, h^2) on a Breit-Wigner
+// one, 0 on a flat one; for iso channels the centres m_0 .. m_{d-1}, then ga^2.
+enum { kChanIso = 1, kChanLin = 2, kChanPair = 4 };
+template <typename T>
+struct __align__(16) ChanHead {
+  uint32_t gmask, bmask;
+  int16_t kind;  // kChanIso | kChanLin | kChanPair
+  int16_t pad_;
+  int16_t ea, eb;
+  T twin, term, bound, look;
+};
+// Behind the constants in FP64: (m, h^2) and the log hint map's constants of a
+// pair channel's Breit-Wigner axes in axis order.
+struct __align__(16) PairCon {
+  double c[4];
+  float h[4];
+};
+template <typename T>
+__host__ __device__ constexpr int chan_pair_at(int d) {
+  return ((int)sizeof(ChanHead<T>) + 2 * d * (int)sizeof(T) + 15) & ~15;
+}
+template <typename T>
+__host__ __device__ constexpr int chan_stride(int d) {
+  return chan_pair_at<T>(d) + (sizeof(T) == 8 ? (int)sizeof(PairCon) : 0);
+}
+
 // One cell of an axis' hint map, precomputed from its p-space edges:
 // J = interior edges whose cell is lower (all of them lie below any x of the
 // cell); with at most one edge inside the cell, e is that edge (+inf if
@@ -226,7 +277,47 @@ struct PeakDim {
 // Math wrappers resolving to the device math library for each precision.
 __device__ inline double m_exp(double x) { return exp(x); }
 __device__ inline float m_exp(float x) { return expf(x); }
-__device__ inline double m_exp2(double x) { return exp2(x); }
+// Coefficients of the FP64 special functions (fp64_fit.py), highest power
+// first.  They are read with scalar loads where they are used (fresh() hides
+// where they come from): as literals the compiler kept them in vector
+// registers across the pass's loop and spilled them there, 40 to 60 scratch
+// reads per evaluation.
+constexpr int kLog2N = 9, kErfcinvN = 26, kSinN = 7, kCosN = 8, kExp2N = 12;
+__device__ const double kErfcinvTab[kLog2N + kErfcinvN] = {  // log2, then the central piece
+    0.17144989425121918, 0.16862072992906546, 0.19239274586704302, 0.22195249899072644,
+    0.26230819523994015, 0.32059889794090296, 0.41219858311123148, 0.5770780163555852,
+    0.96179669392597555,
+    5.839458082047211e-09, -8.0908977213792306e-09, -4.5087329353724268e-08, 9.8676198969758009e-08,
+    8.863055592715813e-08, -4.9361783614262281e-07, 4.6807872055697208e-07, 8.4261207184972158e-07,
+    -3.3435413584532678e-06, 3.7363309444613917e-06, 5.2474671433003046e-06, -2.5758430392203254e-05,
+    3.2960471664389562e-05, 3.3663427339509055e-05, -0.00020245689308002459, 0.00029197778647533143,
+    0.00019691980709171314, -0.0016070752518853547, 0.0026863639308647908, 0.00067461473098120062,
+    -0.01281929971804836, 0.028230934696226413, -0.016552434035712049, -0.10289932479305051,
+    0.88079803173219484, 1.8156662240587476};
+__device__ const double kSinCosTab[kSinN + kCosN] = {
+    1.589457978152985e-10, -2.5050714321896748e-08, 2.7557313359736881e-06, -0.00019841269828602579,
+    0.008333333333320302, -0.16666666666666616, 1,
+    -1.1353266525927744e-11, 2.0875580117542017e-09, -2.7557313080114282e-07, 2.480158728381321e-05,
+    -0.0013888888888860963, 0.041666666666666449, -0.5, 1};
+__device__ const double kExp2Tab[kExp2N] = {
+    4.4566754636398608e-10, 7.0741945626131049e-09, 1.0178051192117847e-07, 1.3215432534254118e-06,
+    1.5252733856295574e-05, 0.00015403530463727982, 0.0013333558146390351, 0.0096181291075872529,
+    0.055504108664821701, 0.24022650695910158, 0.69314718055994529, 1};
+__device__ __forceinline__ CP<double> fresh(const double* p) {
+  asm volatile("" : "+s"(p));
+  return cp(p);
+}
+
+// 2^x for x <= 1 (cut at 3e-18, about 1 ulp; below the exponent range 0).
+__device__ inline double m_exp2(double x) {
+  const CP<double> c = fresh(kExp2Tab);
+  const double n = __builtin_rint(x);
+  const double f = x - n;
+  double P = c[0];
+#pragma unroll
+  for (int i = 1; i < kExp2N; ++i) P = fma(P, f, c[i]);
+  return __builtin_amdgcn_ldexp(P, (int)fmax(n, -4096.0));
+}
 // FP32: the hardware exp2 (one instruction, about 1 ulp; a result below
 // 2^-126 may come back as 0).  Every use is a density kernel
 // 2^(-sum z'^2) <= 1, so such a result is a term at least 2^-126 below the
@@ -237,25 +328,43 @@ __device__ inline float m_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 // 1/x: exact in FP64; the hardware reciprocal (1 ulp) in FP32.
 __device__ inline double m_rcp(double x) { return 1.0 / x; }
 __device__ inline float m_rcp(float x) { return __builtin_amdgcn_rcpf(x); }
-__device__ inline double m_tan(double x) { return tan(x); }
 __device__ inline float m_tan(float x) { return tanf(x); }
 // FP32 erfcinv(y), 0 < y < 2, in the structure of M. Giles' erfinv
 // approximation ("Approximating the erfinv function", GPU Computing Gems,
 // Jade Edition, 2011): with w = -log2(y (2 - y)), erfcinv(y) = erfinv(1 - y)
 // = (1 - y) P(w), P a polynomial in (w - 5) / 5 for w <= 10 (y >= 4.9e-4:
 // all but a few lanes in a thousand) and in a normalised sqrt(w) for
-// 10 < w <= 26; beyond (y < 7.5e-9) the library's erfcinvf.  Coefficients
+// 10 < w <= 26; beyond (y < 7.5e-9) erfcinv_far.  Coefficients
 // fitted by erfcinv_fit.py (largest relative error of the fits 2.9e-08 and
 // 1.7e-08; in FP32 with the hardware log2 about 2.5e-7, median 4e-8).  The
 // library function spends about 110 instructions over its three branches.
-// The library erfcinvf for the far tail, kept out of line (rare; inlined
-// into the branchy fast path it broke this compiler's instruction selection).
-__device__ __noinline__ float erfcinv_far(float y) { return erfcinvf(y); }
+// The far tail, y < 7.5e-9 down to the smallest denormal (2 - y = 2): the same
+// structure on 26 < w <= 151 (fp64_fit.py; 2e-9 of the fit, FP32 rounding
+// above it).  In line: a call here, though never taken, made the kernels save
+// their registers around every axis (34 spilled VGPRs at d = 10).
+__device__ inline float erfcinv_far(float y) {
+  const float w = 63.0f - __builtin_amdgcn_logf(y * 0x1p64f);
+  const float t = (sqrtf(w) - 8.693612621e+00f) * 2.781956039e-01f;
+  float P = 1.396802121e-05f;
+  P = fmaf(P, t, -3.095602143e-05f);
+  P = fmaf(P, t, 3.235408476e-05f);
+  P = fmaf(P, t, -7.128970774e-05f);
+  P = fmaf(P, t, 1.744936948e-04f);
+  P = fmaf(P, t, -3.016682099e-04f);
+  P = fmaf(P, t, 3.495910400e-04f);
+  P = fmaf(P, t, 3.016676134e-04f);
+  P = fmaf(P, t, -4.534591285e-03f);
+  P = fmaf(P, t, 3.017693168e+00f);
+  P = fmaf(P, t, 7.108942973e+00f);
+  return P;
+}
 
+// CENTRAL: the caller knows that w <= 10.
+template <bool CENTRAL = false>
 __device__ inline float fast_erfcinv(float y) {
   const float L = __builtin_amdgcn_logf(y * (2.0f - y));  // log2, -w
   const float x = 1.0f - y;
-  if (L >= -10.0f) {
+  if (CENTRAL || L >= -10.0f) {
     const float t = fmaf(L, -0.2f, -1.0f);
     float P = -1.689334030e-05f;
     P = fmaf(P, t, 1.472581541e-04f);
@@ -286,60 +395,176 @@ __device__ inline float fast_erfcinv(float y) {
   }
   return erfcinv_far(y);
 }
-// FP64 erfcinv: the FP32 value as the start of one Halley step on
-// erfc(x) = y (erfc' = -2/sqrt(pi) e^{-x^2}, erfc'' = -2 x erfc', so the step
-// is x - u / (1 + x u) with u = (erfc(x) - y) / erfc'(x)); from the FP32
-// value's relative error of about 2.5e-7 the step's cubic convergence leaves
-// the rounding of erfc and exp.  Outside the FP32 value's range (y below
-// 1e-37, where FP32 has no normal number near y) the library function.
-// Used by the single-job FP64 pass; the batched pass keeps the library
-// function (with this one inlined it took 155 -> 161 ms on the 256-job
-// batch).
-__device__ inline double m_erfcinv_refined(double y) {
-  if (!(y >= 1e-37 && y <= 1.0)) return erfcinv(y);
-  const double x = (double)fast_erfcinv((float)y);
-  const double u = (erfc(x) - y) / (-1.1283791670955125739 * exp(-x * x));
-  return x - u / (1.0 + x * u);
+// FP64 erfcinv and log2, in the same structure (coefficients: fp64_fit.py; the
+// fits are cut below 5e-17).  A central piece for w = -log2(y (2 - y)) <= 11
+// (y >= 2.4e-4: all but about one lane-axis in 2000) and three pieces in
+// sqrt(w) behind one branch, their coefficients read per lane.  The library's
+// erfcinv (and a Halley step on erfc from the FP32 value before it) spent
+// about 250 instructions and the pass's registers on each axis.
+constexpr double kErfcinvW1 = 11.0;
+constexpr int kErfcinvPieceN = 24;
+__device__ const double kErfcinvPiece[3][kErfcinvPieceN + 2] = {  // centre, 1/half, coefficients
+    {4.6583123951776999, 0.74532998322843202,
+     -1.1086380178806771e-10, 8.5314266200362513e-11, 1.1768159457621137e-09, -3.259827465722147e-09,
+     2.0119847879118342e-09, 1.1639619642971096e-08, -5.287517566442768e-08, 1.0914331496941178e-07,
+     -3.9529159669494931e-08, -4.90894570194495e-07, 1.7433021164541841e-06, -2.975819927228338e-06,
+     1.1041032389988738e-06, 9.5511633350386016e-06, -3.4482603897486704e-05, 7.3909304553016703e-05,
+     -0.00012181629511168777, 0.0001799527282383712, -0.00029702458675398899, 0.00063430187633557907,
+     -0.0014564631710620953, 0.0020063445487988121, 1.1272440282422962, 3.716948227966332},
+    {9, 0.33333333333333331,
+     -2.8525368123130821e-10, 4.0546229939122544e-10, 1.1006065715487956e-09, -1.5490385099566593e-09,
+     -2.1006175675421456e-09, 2.9291320021809486e-09, 1.9649262260689024e-09, -1.8978995890107316e-09,
+     -5.1685973334545114e-09, 1.2938606226043683e-08, -3.2638894957313637e-08, 1.0002834720782859e-07,
+     -2.9947528703455623e-07, 8.6915250855661284e-07, -2.4601982986890966e-06, 6.7401996315247254e-06,
+     -1.7617489575746311e-05, 4.2678461714130274e-05, -8.899365437713163e-05, 0.00011729837643180705,
+     0.00023282738793474716, -0.003095596297196376, 2.517887937388029, 7.3661251922288393},
+    {22.5, 0.095238095238095233,
+     -2.3506526752021451e-09, 4.641785402277912e-09, 4.4005697389502602e-09, -7.7386916137819374e-09,
+     -2.0411417674851032e-08, 3.7945844004507808e-08, -2.1884082748820938e-08, 4.6656216097020564e-08,
+     -1.3846675491085614e-07, 2.5423228846803611e-07, -4.2410404863165673e-07, 7.0871841264722134e-07,
+     -1.0536145477037244e-06, 1.1215274991157444e-06, 3.0239021561088597e-07, -7.1287414703839726e-06,
+     3.0987099709464433e-05, -0.00010503738771968648, 0.0003219617072706045, -0.00093962051585709549,
+     0.0026836974408732152, -0.0076699354856200322, 8.7644443549791156, 18.657407855140697}};
+
+__device__ inline double erfcinv_piece(double w) {
+  const double s = sqrt(w);
+  const double* c = kErfcinvPiece[s < 6.0 ? 0 : s < 12.0 ? 1 : 2];
+  const double t = (s - c[0]) * c[1];
+  double P = c[2];
+#pragma unroll 1
+  for (int i = 3; i < kErfcinvPieceN + 2; ++i) P = fma(P, t, c[i]);
+  return P;
 }
-__device__ inline double m_erfcinv(double x) { return erfcinv(x); }
+
+// G values at once: the Horner chains run side by side and share their
+// coefficients.  w = -log2(q) from q = m 2^e, m in [sqrt(1/2), sqrt(2)), and
+// s = (m - 1) / (m + 1) by a refined reciprocal.
+template <int G>
+__device__ __forceinline__ void erfcinv_group(const double (&y)[G], double (&out)[G]) {
+  const CP<double> c = fresh(kErfcinvTab);
+  double w[G], P[G];
+  {
+    double s[G], z[G];
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+      const double q = y[g] * (2.0 - y[g]);
+      double m = __builtin_amdgcn_frexp_mant(q);
+      int e = __builtin_amdgcn_frexp_exp(q);
+      const bool low = m < 0.70710678118654752440;
+      m = low ? 2.0 * m : m;
+      e = low ? e - 1 : e;
+      const double f = m - 1.0, dd = m + 1.0;
+      double r = __builtin_amdgcn_rcp(dd);
+      r = fma(fma(-dd, r, 1.0), r, r);
+      r = fma(fma(-dd, r, 1.0), r, r);
+      const double s0 = f * r;
+      s[g] = fma(fma(-dd, s0, f), r, s0);
+      z[g] = s[g] * s[g];
+      w[g] = (double)e;
+      P[g] = c[0];
+    }
+#pragma unroll
+    for (int i = 1; i < kLog2N; ++i)
+#pragma unroll
+      for (int g = 0; g < G; ++g) P[g] = fma(P[g], z[g], c[i]);
+#pragma unroll
+    for (int g = 0; g < G; ++g)
+      w[g] = -fma(s[g], fma(z[g], P[g], 2.88539008177792681472), w[g]);
+  }
+  bool far = false;
+  {
+    double t[G];
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+      t[g] = fma(w[g], 2.0 / kErfcinvW1, -1.0);
+      P[g] = c[kLog2N];
+      far |= w[g] > kErfcinvW1;
+    }
+#pragma unroll
+    for (int i = 1; i < kErfcinvN; ++i)
+#pragma unroll
+      for (int g = 0; g < G; ++g) P[g] = fma(P[g], t[g], c[kLog2N + i]);
+  }
+  if (far) {
+#pragma unroll
+    for (int g = 0; g < G; ++g)
+      if (w[g] > kErfcinvW1) P[g] = erfcinv_piece(w[g]);
+  }
+#pragma unroll
+  for (int g = 0; g < G; ++g) out[g] = (1.0 - y[g]) * P[g];
+}
+
+// FP32: the central piece on every value, the others behind one branch.
+template <int G>
+__device__ __forceinline__ void erfcinv_group(const float (&y)[G], float (&out)[G]) {
+  bool far = false;
+#pragma unroll
+  for (int g = 0; g < G; ++g) {
+    out[g] = fast_erfcinv<true>(y[g]);
+    far |= !(__builtin_amdgcn_logf(y[g] * (2.0f - y[g])) >= -10.0f);
+  }
+  if (far) {
+#pragma unroll
+    for (int g = 0; g < G; ++g) out[g] = fast_erfcinv(y[g]);
+  }
+}
+__device__ inline double m_erfcinv(double y) {
+  const double a[1] = {y};
+  double r[1];
+  erfcinv_group<1>(a, r);
+  return r[0];
+}
+
+// tan(a), |a| < pi/2 (the map's angles lie between its poles): sine and cosine
+// of a, or of the distance to the pole from pi/2 in two parts, on [0, pi/4]
+// (fp64_fit.py, cut below 4e-18), and one division.
+__device__ inline double m_tan(double a) {
+  const CP<double> k = fresh(kSinCosTab);
+  const double b = fabs(a);
+  const bool near = b > 0.78539816339744830962;
+  const double r = near ? (1.57079632679489655800 - b) + 6.12323399573676603587e-17 : b;
+  const double z = r * r;
+  double s = k[0], c = k[kSinN];
+#pragma unroll
+  for (int i = 1; i < kSinN; ++i) s = fma(s, z, k[i]);
+#pragma unroll
+  for (int i = 1; i < kCosN; ++i) c = fma(c, z, k[kSinN + i]);
+  s *= r;
+  const double t = (near ? c : s) / (near ? s : c);
+  return a < 0.0 ? -t : t;
+}
 __device__ inline float m_erfcinv(float x) { return fast_erfcinv(x); }
 
 constexpr double kSqrt2 = 1.41421356237309504880;
+
+// The upper or lower tail of a Gaussian axis: y in (0, 1] with erfcinv(y) the
+// distance from the median in units of sqrt(2) sigma, and its sign.
+template <typename T, typename PM>
+__device__ inline T gauss_tail(PM m, T x, T xc, T& sign) {
+  const T t = m->pa + x * m->z;
+  const bool lower = t <= T(0.5);
+  sign = lower ? -T(kSqrt2) : T(kSqrt2);
+  return lower ? T(2) * t : T(2) * (m->qb + xc * m->z);
+}
 
 // Forward map p = phi(x) for one dim.  x and xc = 1 - x are both supplied so
 // the upper tail keeps its relative precision.  Gauss: truncated-normal
 // inverse CDF, evaluated on the tail side of the median.  BW: arctan map; in
 // FP32 near either pole it is written with the distance to the pole so that
-// p - m keeps its precision.  In FP32 each case picks its argument first and
-// then makes a single call of the special function (lanes of a wave that take
-// different cases share that call).  PM: pointer to the axis' DimMap<T>
-// (generic or constant address space).
-// REFINED: in FP64, m_erfcinv_refined in place of the library function.
-template <typename T, typename PM, bool REFINED = false>
+// p - m keeps its precision.  Each case picks its argument first and then makes a single
+// call of the special function (lanes of a wave that take different cases
+// share that call).  PM: pointer to the axis' DimMap<T> (generic or constant
+// address space).
+template <typename T, typename PM>
 __device__ inline T map_forward(PM m, T x, T xc) {
   const int kind = m->kind;
   if (kind == GAUSS) {
-    const T t = m->pa + x * m->z;
-    T zz;
-    if constexpr (sizeof(T) == 4) {
-      const bool lower = t <= T(0.5);
-      const T arg = lower ? T(2) * t : T(2) * (m->qb + xc * m->z);
-      zz = (lower ? -T(kSqrt2) : T(kSqrt2)) * m_erfcinv(arg);
-    } else {  // FP64: two call sites keep the register use of the inlined calls down
-      // (one call site with the argument selected first: 21.7 -> 40.2 ms at
-      // d = 10, 32 channels)
-      if (t <= T(0.5)) {
-        const T y = T(2) * t;
-        zz = -T(kSqrt2) * (REFINED ? m_erfcinv_refined(y) : m_erfcinv(y));
-      } else {
-        const T y = T(2) * (m->qb + xc * m->z);
-        zz = T(kSqrt2) * (REFINED ? m_erfcinv_refined(y) : m_erfcinv(y));
-      }
-    }
-    return m->loc + m->width * zz;
+    T sign;
+    const T arg = gauss_tail<T>(m, x, xc, sign);
+    return m->loc + m->width * (sign * m_erfcinv(arg));
   }
   if (kind == BW) {
-    if (sizeof(T) == 8) return m->loc + m->h * m_tan(m->ta + x * m->th);
+    if constexpr (sizeof(T) == 8) return m->loc + m->h * m_tan(m->ta + x * m->th);
     const T da = m->fa + x * m->th;   // theta + pi/2
     const T db = m->fb + xc * m->th;  // pi/2 - theta
     const T quarter = T(0.78539816339744830962);

@@ -68,11 +68,9 @@ struct JobDev {
   double* pnorm64 = nullptr;
   float* pnorm32 = nullptr;
   // channel c's density shares its exponential with the peak of identical
-  // shape, if any (twin_peak[c], -1 if none): f picks up twin_pn[c] * r_c
+  // shape, if any (twin_peak[c], -1 if none): f picks up its norm times r_c
   int32_t* twin_peak = nullptr;  // [K]
   ChanType* ctype = nullptr;     // [K]: axis kinds of each channel
-  double* twin_pn64 = nullptr;   // [K]
-  float* twin_pn32 = nullptr;    // [K]
   int32_t* orphans = nullptr;    // [P]: peaks no channel shares
   int n_orphan = 0;
   // grids: FP64 master edges; FP32 copy; p-space edges and bin densities in
@@ -87,31 +85,27 @@ struct JobDev {
   // Cell<T> [K][d][M]: per hint cell, its start bin and its single edge (if
   // any) with the densities on either side
   void* ctab = nullptr;
-  // T [K]: per channel, an upper bound of 2^s cnorm_c prod_k max_j dens_kj
-  // (s = 25 in FP32, 54 in FP64), so that alpha_c gbound_c r_c(p) bounds
-  // 2^s times the channel's term of g(p) before its lookups
-  void* gbound = nullptr;
-  // T [3][K]: per channel, (T)alpha_c gbound_c (the term bound's factor),
-  // (T)alpha_c cnorm_c (the factor of the channel's term) and alpha_c cnorm_c
-  // 2^s (1 + m) rounded up (the factor of the bound from looked-up densities),
-  // in the pass precision, for the pass's alpha (written with the
-  // allocation); t_aterm the same for the trace allocation's t_alpha
-  void* aterm = nullptr;
-  void* t_aterm = nullptr;
-  // T [K][d][2]: the density-kernel constants of every axis in the pass
-  // precision, contiguous per channel: (ga, gb) on a Gaussian axis, (m, h^2)
-  // on a Breit-Wigner one, 0 on a flat one
-  void* gab = nullptr;
+  double* axmax = nullptr;   // [K][d]: largest bin density of every axis
+  int* next = nullptr;       // [8] the running pass's next work unit (cleared by the allocation)
+  int* ticket = nullptr;     // channels of the running reduction that are done
+  // ChanHead<T> records [K] with their density-kernel constants behind them
+  // (chan_stride), in the pass precision; t_crec the same for the trace
+  // allocation
+  char* crec = nullptr;
+  char* t_crec = nullptr;
   // float [K][d][2]: the hint-map constants (a, b) of every axis, contiguous
   // per channel: (hs, hb) on channels Gaussian on every axis, (ls, lb) on the
   // others (the map of x starts from a x + b)
   float* hab = nullptr;
-  // int32 [K][2]: per channel, the exponent offsets (EA, EB) of the skip test
-  // of an all-Gaussian channel from a partial exponent (written with the
-  // allocation, as they depend on alpha): the channel's terms of f and g are
-  // below half an ulp of f and g when the partial exponent sum is at least
-  // max(EA - ex(f), EB - ex(g))
-  int32_t* skx = nullptr;
+  // channel masks (single jobs with several channels with a Gaussian axis;
+  // mcv_mask.h): FP16 coefficients [tiles of 32 channels][steps][64 lanes][8],
+  // per channel the offset and factor of its threshold, and the thresholds of
+  // the allocation's weights (padded to whole tiles)
+  void* mco = nullptr;
+  float* moff = nullptr;   // [Kp][2]
+  float* mthr = nullptr;   // [Kp]
+  int masked = 0;          // the job has masks
+  int fpos = 1;            // no channel's peak has a negative weight
   // channel weights and allocation
   double* alpha = nullptr;   // [K]
   int64_t* nc = nullptr;     // [K]
@@ -143,11 +137,11 @@ struct JobSet {
   int prec = 0;                 // precision of every job of the set
   int maxK = 0, maxKd = 0, maxd = 0;
   bool has_eq = false;          // some job has channel equivalences
-  int64_t maxTab = 0, maxCells = 0;
   // sample pass work units: unit u belongs to job j when
   // unit_prefix[j] <= u < unit_prefix[j+1]; nullptr for a set of one job
   const int* unit_prefix = nullptr;
   int n_units = 0;
+  int max_chunks = 1;           // most chunks a channel's slots are summed in (a set with units)
   int* counter = nullptr;       // device work-queue counters [8] (reset by allocate)
   const void* sargs = nullptr;  // device sample-kernel arguments [n] (job precision)
   int block = 1024;             // sample-kernel workgroup size
@@ -166,6 +160,7 @@ inline JobSet single_set(const JobDev& j) {
   js.n = 1;
   js.host = &j;
   js.dev = j.self;
+  js.counter = j.next;
   js.prec = j.prec;
   set_extents(js);
   return js;
@@ -182,45 +177,51 @@ void launch_tables(const JobSet& js, hipStream_t s);
 // allocation (t_nc, t_start, t_alpha) instead and leave alpha alone.
 // Resets the set's 8 work-queue counters.
 void launch_allocate(const JobSet& js, int64_t n_override, bool to_trace, hipStream_t s);
-// Stratified pass (jobs with strat > 0): G work units over the boxes;
-// returns G, or -1.
-int launch_sample_strat(const JobDev& j, int64_t n_points, hipStream_t s);
 // LDS bytes of the single-job sample kernel's layout.
 int sample_lds_bytes(const JobDev& j);
-// The single-job sample pass (a set of one, G workgroups chosen here for
-// n_points calls); returns G, or -1 if the kernel cannot get its LDS.
-int launch_sample(const JobSet& js, int64_t n_points, hipStream_t s);
+// Work units of a pass, and the workgroups that run them (0 if the kernel
+// cannot get its LDS).
+struct Split {
+  int U, G;
+};
+// The single-job sample pass of n_points calls.
+Split launch_sample(const JobDev& j, int64_t n_points, hipStream_t s);
+// Stratified pass (jobs with strat > 0): work units over the boxes.
+Split launch_sample_strat(const JobDev& j, int64_t n_points, hipStream_t s);
 // Batched sample pass: argument record of one job for a workgroup size,
 // written to args_host (sample_args_bytes(prec) bytes); returns the LDS bytes
 // the job's layout uses.
 size_t sample_args_bytes(int prec);
 int sample_queue_layout(const JobDev& j, int block, void* args_host);
-// Single-job sample kernels of each precision (n_points calls; returns the
-// workgroups, or -1 if the kernel cannot get its LDS).
-int launch_sample_f32(const JobDev& j, int64_t n_points, hipStream_t s);
-int launch_sample_f64(const JobDev& j, int64_t n_points, hipStream_t s);
-// Workgroups the single-job sample kernel of each precision runs a pass of
-// n_points with (-1 if it cannot get its LDS).
-int sample_grid_f32(const JobDev& j, int64_t n_points);
-int sample_grid_f64(const JobDev& j, int64_t n_points);
-// The sample kernel's trace instantiation: a pass over the trace allocation
-// with G workgroups at iteration tag `tag`, writing f, g, w (double) of calls
-// [first, first+count) to out[count][3]; nothing else of the state changes
-// except the per-unit partial buffers.  Returns G, or -1.
-int launch_sample_trace_f32(const JobDev& j, int G, uint32_t tag, int64_t first, int64_t count,
-                            double* out, hipStream_t s);
-int launch_sample_trace_f64(const JobDev& j, int G, uint32_t tag, int64_t first, int64_t count,
-                            double* out, hipStream_t s);
-// The same three for jobs drawing from MRG32k3a streams (mrg_f32.hip,
-// mrg_f64.hip); the functions above hand such jobs to these.
-int launch_sample_mrg_f32(const JobDev& j, int64_t n_points, hipStream_t s);
-int launch_sample_mrg_f64(const JobDev& j, int64_t n_points, hipStream_t s);
-int sample_grid_mrg_f32(const JobDev& j, int64_t n_points);
-int sample_grid_mrg_f64(const JobDev& j, int64_t n_points);
-int launch_sample_trace_mrg_f32(const JobDev& j, int G, uint32_t tag, int64_t first,
-                                int64_t count, double* out, hipStream_t s);
-int launch_sample_trace_mrg_f64(const JobDev& j, int G, uint32_t tag, int64_t first,
-                                int64_t count, double* out, hipStream_t s);
+// Single-job sample kernels (single.hip, one object per precision P (1: FP32),
+// dimension bucket D and generator R (1: MRG32k3a)): the pass of n_points
+// calls, and its trace instantiation: the same pass over the trace allocation
+// at iteration tag `tag`, writing f, g, w (double) of calls [first,
+// first+count) to out[count][3]; nothing else of the state changes except the
+// per-unit partial buffers.
+#define MCV_SINGLE_NAME(WHAT, P, D, R) MCV_SINGLE_NAME_(WHAT, P, D, R)
+#define MCV_SINGLE_NAME_(WHAT, P, D, R) single_##WHAT##_##P##_##D##_##R
+#define MCV_SINGLE_DECLARE(P, D, R)                                                             \
+  Split MCV_SINGLE_NAME(launch, P, D, R)(const JobDev& j, int64_t n_points, hipStream_t s);     \
+  Split MCV_SINGLE_NAME(trace, P, D, R)(const JobDev& j, int64_t n_points, uint32_t tag,        \
+                                        int64_t first, int64_t count, double* out,              \
+                                        hipStream_t s);
+#define MCV_SINGLE_DECLARE_D(D) \
+  MCV_SINGLE_DECLARE(0, D, 0)   \
+  MCV_SINGLE_DECLARE(0, D, 1)   \
+  MCV_SINGLE_DECLARE(1, D, 0)   \
+  MCV_SINGLE_DECLARE(1, D, 1)
+MCV_SINGLE_DECLARE_D(2)
+MCV_SINGLE_DECLARE_D(4)
+MCV_SINGLE_DECLARE_D(6)
+MCV_SINGLE_DECLARE_D(8)
+MCV_SINGLE_DECLARE_D(10)
+MCV_SINGLE_DECLARE_D(12)
+MCV_SINGLE_DECLARE_D(16)
+MCV_SINGLE_DECLARE_D(32)
+// The same by the job's precision, dimension and generator (sample.hip).
+Split single_trace(const JobDev& j, int64_t n_points, uint32_t tag, int64_t first, int64_t count,
+                   double* out, hipStream_t s);
 // Batched sample kernels (queue.hip, one object per precision P (1: FP32),
 // launch bound LB and term-bound option TB): the kernel for a set whose
 // largest dimension is maxd.
@@ -245,8 +246,11 @@ int launch_sample_queue(const JobSet& js, hipStream_t s);
 // Per-channel and total reduction of the pass into each job's history row
 // *iter_dev, which is then incremented; G for a set of one.
 void launch_finalize(const JobSet& js, int G, hipStream_t s);
-void launch_refine_grid(const JobSet& js, hipStream_t s);
-void launch_update_alpha(const JobSet& js, hipStream_t s);
+// Chunks that a channel's slots are summed in, for a pass of G units.
+int finalize_chunks(int64_t G, int K);
+// Rebins every grid (and forms its tables) and / or updates the channel
+// weights.
+void launch_refine(const JobSet& js, bool grid, bool alpha, hipStream_t s);
 // Trace of calls [first, first+count) with the trace allocation.
 void launch_trace(const JobDev& j, uint32_t tag, int64_t first, int64_t count, int n_words,
                   uint32_t* words, int32_t* chan, int32_t* bins, double* p, double* fgw,

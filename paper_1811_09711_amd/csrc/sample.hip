@@ -1,7 +1,6 @@
 // Host side of the sample pass (argument records, launches of the
-// single-job kernels instantiated in single_f32.hip / single_f64.hip and of
-// the batched queue kernels in queue_f32.hip / queue_f64.hip), plus the
-// per-call trace and the unweighting trial kernels that share its point
+// single-job kernels instantiated by single.hip and of the batched queue
+// kernels instantiated by queue.hip), plus the per-call trace and the unweighting trial kernels that share its point
 // evaluation.
 //
 // Brass, Kilian, Reuter, arXiv:1811.09711, Sec. 3.5: for every call r_c of
@@ -351,16 +350,36 @@ void unweight_f32(const JobDev& j, uint64_t q0, int64_t count, const double* wma
 int sample_lds_bytes(const JobDev& j) {
   if (j.prec == 1) {
     SampleArgs<float> a = make_args<float>(j, 0);
-    return lds_layout<float>(a, Tune<float>::BLOCK / 64);
+    return lds_layout<float>(a, Tune<float>::BLOCK / 64, 0, j.masked != 0);
   }
   SampleArgs<double> a = make_args<double>(j, 0);
-  return lds_layout<double>(a, Tune<double>::BLOCK / 64);
+  return lds_layout<double>(a, Tune<double>::BLOCK / 64, 0, j.masked != 0);
 }
 
-int launch_sample(const JobSet& js, int64_t n_points, hipStream_t s) {
-  if (js.n != 1) return -1;
-  const JobDev& j = js.host[0];
-  return j.prec == 1 ? launch_sample_f32(j, n_points, s) : launch_sample_f64(j, n_points, s);
+#define MCV_SINGLE_PR(WHAT, D, ...)                                                  \
+  (j.prec == 1 ? (j.rng ? MCV_SINGLE_NAME(WHAT, 1, D, 1)(__VA_ARGS__)                \
+                        : MCV_SINGLE_NAME(WHAT, 1, D, 0)(__VA_ARGS__))               \
+               : (j.rng ? MCV_SINGLE_NAME(WHAT, 0, D, 1)(__VA_ARGS__)                \
+                        : MCV_SINGLE_NAME(WHAT, 0, D, 0)(__VA_ARGS__)))
+#define MCV_SINGLE_CALL(WHAT, ...)                               \
+  do {                                                           \
+    if (j.d <= 2) return MCV_SINGLE_PR(WHAT, 2, __VA_ARGS__);    \
+    if (j.d <= 4) return MCV_SINGLE_PR(WHAT, 4, __VA_ARGS__);    \
+    if (j.d <= 6) return MCV_SINGLE_PR(WHAT, 6, __VA_ARGS__);    \
+    if (j.d <= 8) return MCV_SINGLE_PR(WHAT, 8, __VA_ARGS__);    \
+    if (j.d <= 10) return MCV_SINGLE_PR(WHAT, 10, __VA_ARGS__);  \
+    if (j.d <= 12) return MCV_SINGLE_PR(WHAT, 12, __VA_ARGS__);  \
+    if (j.d <= 16) return MCV_SINGLE_PR(WHAT, 16, __VA_ARGS__);  \
+    return MCV_SINGLE_PR(WHAT, 32, __VA_ARGS__);                 \
+  } while (0)
+
+Split launch_sample(const JobDev& j, int64_t n_points, hipStream_t s) {
+  MCV_SINGLE_CALL(launch, j, n_points, s);
+}
+
+Split single_trace(const JobDev& j, int64_t n_points, uint32_t tag, int64_t first, int64_t count,
+                   double* out, hipStream_t s) {
+  MCV_SINGLE_CALL(trace, j, n_points, tag, first, count, out, s);
 }
 
 size_t sample_args_bytes(int prec) {

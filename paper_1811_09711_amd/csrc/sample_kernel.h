@@ -11,15 +11,16 @@
 #pragma once
 
 #include <hip/hip_runtime.h>
+#include <math.h>
 #include <string.h>
 
 #include "mcv_internal.h"
+#include "mcv_mask.h"
 #include "mcv_point.h"
 
 namespace mcv {
 
 namespace {
-
 
 template <typename T>
 struct SampleArgs {
@@ -27,27 +28,28 @@ struct SampleArgs {
   int sT;               // per-axis table stride (entries)
   int M, mshift;        // hint cells per axis and the log map's shift
   int n_orphan;
-  int off_own, off_hist, off_red;
+  int off_own, off_hist, off_red, off_queue;
   uint32_t tag;         // iteration tag of trace and unweighting launches
   uint64_t seed;
   const int32_t* iter;  // sample pass: completed passes = this pass's tag
+  int units;            // single-job pass: work units, and the next one to take
+  int* next;
   const int64_t* start;
   const double* alpha;
   const DimMap<T>* cmap;
-  const ChanType* ctype;
   const T* cnorm;
-  const T* twin_pn;
   const PeakDim<T>* pmap;
   const T* pnorm;
   const int32_t* orphans;
   const Pair<T>* xtab;   // [K][d][sT]
   const Pair<T>* ptab;   // [K][d][sT]
   const Cell<T>* ctab;   // [K][d][M]
-  const T* gbound;       // [K]
-  const T* aterm;        // [3][K]: (T)alpha_c gbound_c, (T)alpha_c cnorm_c, alpha_c cnorm_c 2^s(1+m)
-  const T* gab;          // [K][d][2] density-kernel constants
+  const char* crec;      // [K] channel records (ChanHead)
+  int cstride;           // bytes of a record
   const float* hab;      // [K][d][2] hint-map constants
-  const int32_t* skx;    // [K][2] partial-exponent skip offsets
+  const void* mco;       // channel-mask coefficients (mcv_mask.h)
+  const float* mthr;     // [K rounded up to 32] channel-mask thresholds
+  int fpos;              // no channel's peak has a negative weight
   double* part;
   double* hpart;
   // trace instantiation only: f, g, w of calls [tr_first, tr_first + tr_count)
@@ -60,6 +62,26 @@ struct SampleArgs {
   const int64_t* spb;    // [K] calls per box
   const int64_t* bstart; // [K+1] box prefix
 };
+
+// Channel cc's record, and the constants behind it.
+template <typename T>
+__device__ __forceinline__ CP<ChanHead<T>> chan_at(const SampleArgs<T>& a, int cc) {
+  return (CP<ChanHead<T>>)(cp(a.crec) + (size_t)cc * a.cstride);
+}
+template <typename T>
+__device__ __forceinline__ CP<T> chan_con(CP<ChanHead<T>> h) {
+  return (CP<T>)(h + 1);
+}
+template <typename T>
+__device__ __forceinline__ CP<PairCon> pair_con(CP<ChanHead<T>> h, int d) {
+  return (CP<PairCon>)((CP<char>)h + chan_pair_at<T>(d));
+}
+template <typename T, int MAXD, bool PAIR = false>
+__device__ __forceinline__ T chan_r_of(CP<ChanHead<T>> h, int d, const T (&p)[MAXD]) {
+  if constexpr (PAIR)
+    if (h->kind & kChanPair) return pair_r<T, MAXD>(&pair_con(h, d)->c[0], h->bmask, d, p);
+  return chan_r<T, MAXD>(chan_con(h), h->kind & kChanIso, h->gmask, h->bmask, d, p);
+}
 
 // Stratified sampling: bin j and fraction of one axis from the box digit b
 // and the word u: r = (b + u 2^-32) / nr as the fixed-point R = b 2^32 + u
@@ -121,59 +143,89 @@ __device__ __forceinline__ void draw_words(uint64_t seed, uint64_t i, uint32_t t
 
 // Forward part of one call of channel c: bins, x, p = phi_c(x) and the own
 // grid density prod_k 1/(n Delta) (eq. g(x)), from the channel's x-space
-// (edge, density) tables ot (per-axis stride sT).
-template <typename T, int MAXD, bool REFINED = false>
-__device__ inline T forward_point(const uint32_t (&u)[MAXD], int d, int n, CP<DimMap<T>> cm,
-                                  const Pair<T>* ot, int sT, T (&p)[MAXD],
-                                  uint32_t (&jpack)[(MAXD + 3) / 4]) {
+// (edge, density) tables ot (per-axis stride sT).  bin(k, j, fr) gives axis
+// k's bin and fraction.  gauss: the channel is Gaussian on every axis (the
+// same on every lane); in FP64 its axes are then mapped a few at a time, so
+// that their inverse error functions run side by side.
+template <typename T, int MAXD, bool GROUPED, typename Bin>
+__device__ __forceinline__ T forward_axes(const Bin& bin, int d, CP<DimMap<T>> cm,
+                                          const Pair<T>* ot, int sT, bool gauss, T (&p)[MAXD],
+                                          uint32_t (&jpack)[(MAXD + 3) / 4]) {
+  constexpr int GD = !GROUPED ? 1 : MAXD <= 4 ? MAXD : MAXD % 5 == 0 ? 5 : MAXD % 4 == 0 ? 4 : MAXD % 3 == 0 ? 3 : 1;
+  static_assert(MAXD % GD == 0, "groups of whole axes");
   T own = T(1);
 #pragma unroll
   for (int k = 0; k < (MAXD + 3) / 4; ++k) jpack[k] = 0u;
 #pragma unroll
-  for (int k = 0; k < MAXD; ++k) {
-    if (k < d) {
-      const uint32_t j = __umulhi(u[k], (uint32_t)n);
-      const uint32_t lo = u[k] * (uint32_t)n;
-      const T fr = Frac<T>::get(lo);
-      const Pair<T> a0 = ot[k * sT + j], a1 = ot[k * sT + j + 1];
-      const T w = a1.e - a0.e;
-      const T x = a0.e + fr * w;
-      const T xc = (T(1) - a1.e) + (T(1) - fr) * w;
-      p[k] = map_forward<T, CP<DimMap<T>>, REFINED>(cm + k, x, xc);
-      own *= a0.dens;
-      jpack[k >> 2] |= j << (8 * (k & 3));
+  for (int k0 = 0; k0 < MAXD; k0 += GD) {
+    T x[GD], xc[GD];
+#pragma unroll
+    for (int g = 0; g < GD; ++g) {
+      const int k = k0 + g;
+      x[g] = xc[g] = T(0.5);
+      if (k < d) {
+        uint32_t j;
+        T fr;
+        bin(k, j, fr);
+        const Pair<T> a0 = ot[k * sT + j], a1 = ot[k * sT + j + 1];
+        const T w = a1.e - a0.e;
+        x[g] = a0.e + fr * w;
+        xc[g] = (T(1) - a1.e) + (T(1) - fr) * w;
+        own *= a0.dens;
+        jpack[k >> 2] |= j << (8 * (k & 3));
+      }
+    }
+    if (GD > 1 && gauss) {
+      if constexpr (GD > 1) {
+        T y[GD], sign[GD], z[GD];
+#pragma unroll
+        for (int g = 0; g < GD; ++g) {
+          y[g] = T(1);
+          if (k0 + g < d) y[g] = gauss_tail<T>(cm + k0 + g, x[g], xc[g], sign[g]);
+        }
+        erfcinv_group<GD>(y, z);
+#pragma unroll
+        for (int g = 0; g < GD; ++g) {
+          const int k = k0 + g;
+          p[k] = T(0);
+          if (k < d) p[k] = cm[k].loc + cm[k].width * (sign[g] * z[g]);
+        }
+      }
     } else {
-      p[k] = T(0);
+#pragma unroll
+      for (int g = 0; g < GD; ++g) {
+        const int k = k0 + g;
+        p[k] = T(0);
+        if (k < d) p[k] = map_forward<T>(cm + k, x[g], xc[g]);
+      }
     }
   }
   return own;
 }
 
+template <typename T, int MAXD, bool GROUPED>
+__device__ inline T forward_point(const uint32_t (&u)[MAXD], int d, int n, CP<DimMap<T>> cm,
+                                  const Pair<T>* ot, int sT, bool gauss, T (&p)[MAXD],
+                                  uint32_t (&jpack)[(MAXD + 3) / 4]) {
+  return forward_axes<T, MAXD, GROUPED>(
+      [&](int k, uint32_t& j, T& fr) {
+        j = __umulhi(u[k], (uint32_t)n);
+        fr = Frac<T>::get(u[k] * (uint32_t)n);
+      },
+      d, cm, ot, sT, gauss, p, jpack);
+}
+
 // The same from given bins and fractions (stratified sampling).
-template <typename T, int MAXD>
+template <typename T, int MAXD, bool GROUPED>
 __device__ inline T forward_point_jf(const uint32_t (&jj)[MAXD], const T (&frs)[MAXD], int d,
-                                     CP<DimMap<T>> cm, const Pair<T>* ot, int sT, T (&p)[MAXD],
-                                     uint32_t (&jpack)[(MAXD + 3) / 4]) {
-  T own = T(1);
-#pragma unroll
-  for (int k = 0; k < (MAXD + 3) / 4; ++k) jpack[k] = 0u;
-#pragma unroll
-  for (int k = 0; k < MAXD; ++k) {
-    if (k < d) {
-      const uint32_t j = jj[k];
-      const T fr = frs[k];
-      const Pair<T> a0 = ot[k * sT + j], a1 = ot[k * sT + j + 1];
-      const T w = a1.e - a0.e;
-      const T x = a0.e + fr * w;
-      const T xc = (T(1) - a1.e) + (T(1) - fr) * w;
-      p[k] = map_forward<T>(cm + k, x, xc);
-      own *= a0.dens;
-      jpack[k >> 2] |= j << (8 * (k & 3));
-    } else {
-      p[k] = T(0);
-    }
-  }
-  return own;
+                                     CP<DimMap<T>> cm, const Pair<T>* ot, int sT, bool gauss,
+                                     T (&p)[MAXD], uint32_t (&jpack)[(MAXD + 3) / 4]) {
+  return forward_axes<T, MAXD, GROUPED>(
+      [&](int k, uint32_t& j, T& fr) {
+        j = jj[k];
+        fr = frs[k];
+      },
+      d, cm, ot, sT, gauss, p, jpack);
 }
 
 // ---------------------------------------------------------------------------
@@ -188,18 +240,15 @@ __device__ __forceinline__ void eval_channels(const SampleArgs<T>& a, const doub
   const int d = a.d, n = a.n, K = a.K;
   CP<double> alpha = cp(alpha_g);
   CP<DimMap<T>> cmap = cp(a.cmap);
-  CP<ChanType> ctype = cp(a.ctype);
   CP<T> cnorm = cp(a.cnorm);
-  CP<T> twin = cp(a.twin_pn);
-  CP<T> gab = cp(a.gab);
   CP<float> hab = cp(a.hab);
   const int sT = a.sT;
   f = T(0);
   g = T(0);
   for (int cc = 0; cc < K; ++cc) {
-    CP<T> gab_cc = gab + (size_t)cc * 2 * d;
-    const T r = chan_r<T, MAXD>(gab_cc, ctype[cc].iso, ctype[cc].gmask, ctype[cc].bmask, d, p);
-    f += twin[cc] * r;
+    const CP<ChanHead<T>> h = chan_at(a, cc);
+    const T r = chan_r_of<T, MAXD>(h, d, p);
+    f += h->twin * r;
     const T qd = cnorm[cc] * r;
     T Gd = T(1);
     if (cc == c) {
@@ -210,7 +259,7 @@ __device__ __forceinline__ void eval_channels(const SampleArgs<T>& a, const doub
       int jb[MAXD];
       const Pair<T>* T0 = a.ptab + (size_t)cc * d * sT;
       const Cell<T>* C0 = a.ctab + (size_t)cc * d * a.M;
-      Gd = ctype[cc].lin
+      Gd = h->kind & kChanLin
                ? grid_density<T, MAXD, 1, true>(T0, C0, sT, n, d, a.M, a.mshift,
                                                 hab + (size_t)cc * 2 * d, p, jb)
                : grid_density<T, MAXD, 1, false>(T0, C0, sT, n, d, a.M, a.mshift,
@@ -234,8 +283,8 @@ __device__ __forceinline__ void eval_call(const SampleArgs<T>& a, const double* 
                                           const uint32_t (&u)[MAXD], T (&p)[MAXD], T& f, T& g,
                                           int32_t* bins /* [K][d] or null */) {
   uint32_t jp[(MAXD + 3) / 4];
-  const T own = forward_point<T, MAXD>(u, a.d, a.n, cp(a.cmap) + (size_t)c * a.d,
-                                       a.xtab + (size_t)c * a.d * a.sT, a.sT, p, jp);
+  const T own = forward_point<T, MAXD, false>(u, a.d, a.n, cp(a.cmap) + (size_t)c * a.d,
+                                       a.xtab + (size_t)c * a.d * a.sT, a.sT, false, p, jp);
   eval_channels<T, MAXD>(a, alpha_g, c, own, jp, p, f, g, bins);
 }
 
@@ -245,8 +294,8 @@ __device__ __forceinline__ void eval_call_jf(const SampleArgs<T>& a, const doubl
                                              const uint32_t (&jj)[MAXD], const T (&fr)[MAXD],
                                              T (&p)[MAXD], T& f, T& g, int32_t* bins) {
   uint32_t jp[(MAXD + 3) / 4];
-  const T own = forward_point_jf<T, MAXD>(jj, fr, a.d, cp(a.cmap) + (size_t)c * a.d,
-                                          a.xtab + (size_t)c * a.d * a.sT, a.sT, p, jp);
+  const T own = forward_point_jf<T, MAXD, false>(jj, fr, a.d, cp(a.cmap) + (size_t)c * a.d,
+                                          a.xtab + (size_t)c * a.d * a.sT, a.sT, false, p, jp);
   eval_channels<T, MAXD>(a, alpha_g, c, own, jp, p, f, g, bins);
 }
 
@@ -269,6 +318,55 @@ __device__ inline uint64_t shfl_xor_u64(uint64_t v, int off) {
   return (uint64_t)lo | ((uint64_t)hi << 32);
 }
 
+// Whether channel cc's term can change gg: terms are non-negative, so gg only
+// grows, and a term below half an ulp of gg leaves it unchanged: skipping such
+// a term gives the same gg as adding it.  (alpha gbound) r < gg bounds the
+// term by gg 2^-25 (FP32; 2^-54 in FP64), below half an ulp.  Exactly zero
+// terms are skipped as well.  The factors (T)alpha gbound and (T)alpha cnorm
+// come formed with the allocation.
+template <typename T, bool TB>
+__device__ __forceinline__ bool term_counts(CP<ChanHead<T>> h, T r, T gg) {
+  return r != T(0) && !(TB && h->bound * r < gg);
+}
+
+// Adds channel cc's term alpha G q to gg: d lookups for G.
+// LAZY: crowded cells first give their largest density (an upper bound of G);
+// the exact walks run only on the lanes where that bound, in the same test
+// with the looked-up densities in place of the maxima, shows the term able to
+// change gg.  Elsewhere the term is below half an ulp of gg, exact or not, and
+// gg is unchanged.
+template <typename T, int MAXD, int GROUP, bool EXACT, bool LAZY, bool PAIR>
+__device__ __forceinline__ void add_term(const SampleArgs<T>& a, int cc, int d, int M, int mshift,
+                                         T r, const T (&p)[MAXD], const uint32_t (&flat)[MAXD],
+                                         T& gg) {
+  const int n = a.n, sT = a.sT;
+  const int chT = d * sT, chC = d * M;  // entries per channel table, cells per channel
+  const CP<ChanHead<T>> h = chan_at(a, cc);
+  GP<Pair<T>> T0 = gptr(a.ptab + (size_t)cc * chT);
+  GP<Cell<T>> C0 = gptr(a.ctab + (size_t)cc * chC);
+  CP<float> hab_cc = cp(a.hab) + (size_t)cc * 2 * d;
+  if constexpr (PAIR) {
+    if (h->kind & kChanPair) {
+      const T Gd = pair_density<T, MAXD, GROUP, EXACT>(T0, C0, sT, n, d, M, mshift,
+                                                       &pair_con(h, d)->h[0], h->bmask, flat, p);
+      gg = fma(h->term * Gd, r, gg);
+      return;
+    }
+  }
+  const bool lin = h->kind & kChanLin;
+  bool crowded = false;
+  T Gd = lin ? grid_density<T, MAXD, GROUP, true, EXACT, LAZY>(T0, C0, sT, n, d, M, mshift, hab_cc,
+                                                              p, nullptr, &crowded)
+             : grid_density<T, MAXD, GROUP, false, EXACT, LAZY>(T0, C0, sT, n, d, M, mshift, hab_cc,
+                                                               p, nullptr, &crowded);
+  if (LAZY && crowded && !(h->look * r * Gd < gg))
+    Gd = lin ? grid_density<T, MAXD, GROUP, true, EXACT>(T0, C0, sT, n, d, M, mshift, hab_cc, p,
+                                                         nullptr)
+             : grid_density<T, MAXD, GROUP, false, EXACT>(T0, C0, sT, n, d, M, mshift, hab_cc, p,
+                                                          nullptr);
+  gg = fma(h->term * Gd, r, gg);
+}
+
 // Every other channel's terms of one call of channel c at point p (eq. g(p)
 // and the integrand's peaks): f += twin r for each channel's density kernel
 // r, gg += alpha G q for the terms that can change gg (reading R25: exactly
@@ -278,27 +376,21 @@ __device__ inline uint64_t shfl_xor_u64(uint64_t v, int off) {
 // MAXD.  M, mshift: the job's hint cells per axis and the log map's shift.
 // LAZY (with TB): crowded hint cells are walked only where their bound
 // cannot rule the term out (see below).
-template <typename T, int MAXD, int GROUP, bool EXACT, bool TB, bool LAZY = false>
+template <typename T, int MAXD, int GROUP, bool EXACT, bool TB, bool LAZY = false, bool PAIR = false>
 __device__ __forceinline__ void other_terms(const SampleArgs<T>& a, int c, int d, int M,
                                             int mshift, const T (&p)[MAXD], T& f, T& gg) {
-  const int n = a.n, K = a.K, sT = a.sT;
-  const int chT = d * sT, chC = d * M;  // entries per channel table, cells per channel
-  CP<ChanType> ctype = cp(a.ctype);
-  CP<T> twin = cp(a.twin_pn);
+  const int K = a.K;
   CP<PeakDim<T>> pmap = cp(a.pmap);
   CP<T> pnorm = cp(a.pnorm);
-  CP<T> aterm = cp(a.aterm);
-  CP<T> gab = cp(a.gab);
-  CP<float> hab = cp(a.hab);
-  CP<int32_t> skx = cp(a.skx);
   CP<int32_t> orphans = cp(a.orphans);
+  uint32_t flat[MAXD];
+  if constexpr (PAIR) flat_cells<T, MAXD>(d, M, mshift, p, flat);
   for (int cc = 0; cc < K; ++cc) {
     if (cc == c) continue;
-    const int iso = ctype[cc].iso;
-    const uint32_t bm = ctype[cc].bmask;
-    CP<T> gab_cc = gab + (size_t)cc * 2 * d;
+    const CP<ChanHead<T>> h = chan_at(a, cc);
     T r;
-    if (TB && sizeof(T) == 8 && iso) {
+    if (TB && sizeof(T) == 8 && (h->kind & kChanIso)) {
+      const CP<T> gab_cc = chan_con(h);
       // The exponent of the first kPartial axes bounds r from above
       // (the full sum only adds non-negative terms): when that bound
       // shows, on every lane of the wavefront, both of the channel's
@@ -318,8 +410,7 @@ __device__ __forceinline__ void other_terms(const SampleArgs<T>& a, int c, int d
           gs = fma(z, z, gs);
         }
       }
-      const int thr = max(skx[2 * cc] - floor_log2_normal(f),
-                          skx[2 * cc + 1] - floor_log2_normal(gg));
+      const int thr = max(h->ea - floor_log2_normal(f), h->eb - floor_log2_normal(gg));
       if (__all(gs * sc >= (T)thr)) continue;
 #pragma unroll
       for (int k = kPartial; k < MAXD; ++k) {
@@ -330,40 +421,150 @@ __device__ __forceinline__ void other_terms(const SampleArgs<T>& a, int c, int d
       }
       r = m_exp2(-(gs * sc));
     } else {
-      r = chan_r<T, MAXD>(gab_cc, iso, ctype[cc].gmask, bm, d, p);
+      r = chan_r_of<T, MAXD, PAIR>(h, d, p);
     }
-    f += twin[cc] * r;
-    // The term alpha G q of channel cc needs G (d lookups) only when it
-    // can change gg.  Terms are non-negative, so gg only grows, and a
-    // term below half an ulp of gg leaves it unchanged: skipping such a
-    // term gives the same gg as adding it.  (alpha gbound) r < gg
-    // bounds the term by gg 2^-25 (FP32; 2^-54 in FP64), below half an
-    // ulp.  Exactly zero terms are skipped as well.  The factors
-    // (T)alpha gbound and (T)alpha cnorm come formed with the allocation.
-    if (r != T(0) && !(TB && aterm[cc] * r < gg)) {
-      GP<Pair<T>> T0 = gptr(a.ptab + (size_t)cc * chT);
-      GP<Cell<T>> C0 = gptr(a.ctab + (size_t)cc * chC);
-      CP<float> hab_cc = hab + (size_t)cc * 2 * d;
-      const bool lin = ctype[cc].lin;
-      // LAZY: crowded cells first give their largest density (an upper bound
-      // of G); the exact walks run only on the lanes where that bound, in the
-      // same test with the looked-up densities in place of the maxima, shows
-      // the term able to change gg.  Elsewhere the term is below half an ulp
-      // of gg, exact or not, and gg is unchanged.
-      static_assert(!LAZY || TB, "the lazy walks rest on the term bound");
-      bool crowded = false;
-      T Gd = lin ? grid_density<T, MAXD, GROUP, true, EXACT, LAZY>(T0, C0, sT, n, d, M, mshift,
-                                                                  hab_cc, p, nullptr, &crowded)
-                 : grid_density<T, MAXD, GROUP, false, EXACT, LAZY>(T0, C0, sT, n, d, M, mshift,
-                                                                   hab_cc, p, nullptr, &crowded);
-      if (LAZY && crowded && !(aterm[2 * K + cc] * r * Gd < gg))
-        Gd = lin ? grid_density<T, MAXD, GROUP, true, EXACT>(T0, C0, sT, n, d, M, mshift, hab_cc,
-                                                             p, nullptr)
-                 : grid_density<T, MAXD, GROUP, false, EXACT>(T0, C0, sT, n, d, M, mshift,
-                                                              hab_cc, p, nullptr);
-      gg += aterm[K + cc] * Gd * r;
-    }
+    f += h->twin * r;
+    static_assert(!LAZY || TB, "the lazy walks rest on the term bound");
+    if (term_counts<T, TB>(h, r, gg))
+      add_term<T, MAXD, GROUP, EXACT, LAZY, PAIR>(a, cc, d, M, mshift, r, p, flat, gg);
   }
+  for (int o = 0; o < a.n_orphan; ++o) {
+    const int i2 = orphans[o];
+    f += pnorm[i2] * peak_r<T, MAXD>(pmap + (size_t)i2 * d, d, p);
+  }
+}
+
+// Lookups of one wavefront put off and done together.  A channel whose term
+// counts on some lanes leaves its (lane, channel) pairs in the wavefront's LDS
+// queue of 64 entries; a full queue, or the last channel, runs one entry per
+// lane: the entry's lane fetches the owner's point across lanes and the
+// channel's records, and leaves alpha cnorm G beside the kernel r; the owners
+// then add their terms in channel order with the operation of add_term, so gg
+// is the same bit for bit (a term tested against an earlier gg counts where
+// it could not change the later one: adding it changes nothing).  At d = 10,
+// 32 channels (24 Gaussian, 8 Breit-Wigner ridges) a wavefront needs 4.4
+// channels' lookups on 11 lanes each: one pass in place of 4.4.
+template <typename T>
+struct WaveQueue {
+  uint32_t who[64];  // owner lane, channel << 6
+  T r[64], ag[64];
+};
+
+template <typename T>
+__device__ __forceinline__ T lane_read(T v, int src) {
+  if constexpr (sizeof(T) == 4) {
+    return __builtin_bit_cast(
+        float, __builtin_amdgcn_ds_bpermute(src << 2, __builtin_bit_cast(int, v)));
+  } else {
+    const uint64_t b = __builtin_bit_cast(uint64_t, v);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_ds_bpermute(src << 2, (int)(uint32_t)b);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_ds_bpermute(src << 2, (int)(uint32_t)(b >> 32));
+    return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+  }
+}
+
+template <typename T, int MAXD, int GROUP, bool EXACT>
+struct PendingTerms {
+  WaveQueue<T>* q;  // this wavefront's
+  int nq = 0, np = 0;    // entries, channels (uniform)
+  int mlo = 0, mhi = 0;  // lane i: the lanes of the queue's channel i
+
+  __device__ __forceinline__ void push(int cc, uint64_t lanes, bool mine, T r) {
+    const int lane = (int)__lane_id();
+    const int pos = nq + __builtin_amdgcn_mbcnt_hi((uint32_t)(lanes >> 32),
+                                                   __builtin_amdgcn_mbcnt_lo((uint32_t)lanes, 0));
+    if (mine) {
+      q->who[pos] = (uint32_t)lane | ((uint32_t)cc << 6);
+      q->r[pos] = r;
+    }
+    if (lane == np) {
+      mlo = (int)(uint32_t)lanes;
+      mhi = (int)(uint32_t)(lanes >> 32);
+    }
+    ++np;
+    nq += __popcll(lanes);
+  }
+
+  __device__ __forceinline__ void run(const SampleArgs<T>& a, int d, int M, int mshift,
+                                      const T (&p)[MAXD], T& gg) {
+    if (nq == 0) return;
+    const int lane = (int)__lane_id();
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    const bool live = lane < nq;
+    const uint32_t who = live ? q->who[lane] : (uint32_t)lane;
+    const T re = live ? q->r[lane] : T(0);
+    const int src = (int)(who & 63u), cc = (int)(who >> 6);
+    T pe[MAXD];
+#pragma unroll
+    for (int k = 0; k < MAXD; ++k)
+      if (EXACT || k < d) pe[k] = lane_read(p[k], src);
+      else pe[k] = T(0);
+    const T ge = lane_read(gg, src);
+    if (live) {
+      const GP<ChanHead<T>> h = (GP<ChanHead<T>>)(gptr(a.crec) + (uint32_t)(cc * a.cstride));
+      const T term = h->term;
+      const T G = lane_density<T, MAXD, GROUP, EXACT>(gptr(a.ptab), gptr(a.ctab), gptr(a.hab), cc,
+                                                      (h->kind & kChanLin) != 0, a.sT, a.n, d, M, mshift,
+                                                      pe, h->look * re, ge);
+      q->ag[lane] = term * G;
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    int base = 0;
+    for (int i = 0; i < np; ++i) {
+      const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane(mlo, i);
+      const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane(mhi, i);
+      const int pos = base + __builtin_amdgcn_mbcnt_hi(hi, __builtin_amdgcn_mbcnt_lo(lo, 0));
+      const uint64_t m = ((uint64_t)hi << 32) | lo;
+      if ((m >> lane) & 1ull) gg = fma(q->ag[pos], q->r[pos], gg);
+      base += __popcll(m);
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    nq = 0;
+    np = 0;
+  }
+};
+
+// The same with the channels that cannot change f or g on any lane of the
+// wavefront left out up front (mcv_mask.h): f and gg enter with the call's own
+// terms, both only grow from there (fpos), so a term below half an ulp of
+// them now is below it when its turn comes; and with the lookups of sparse
+// terms done together (PendingTerms).  Every lane of the wavefront takes part.
+template <typename T, int MAXD, int GROUP, bool EXACT>
+__device__ __forceinline__ void masked_terms(const SampleArgs<T>& a, int c, int d, int M,
+                                             int mshift, WaveQueue<T>* queue, const T (&p)[MAXD],
+                                             T& f, T& gg) {
+  const int K = a.K;
+  const int least = sizeof(T) == 4 ? -126 : -1022;
+  const int e = a.fpos ? min(floor_log2_normal(f), floor_log2_normal(gg)) : least;
+  PendingTerms<T, MAXD, GROUP, EXACT> pend{queue};
+  int base = -32;  // the tile of channels that m is of
+  uint32_t m = 0;
+  bool last = false;
+  do {
+    for (;;) {
+      if (m == 0) {
+        base += 32;
+        last = base >= K;
+        if (last) break;
+        m = channel_mask<MAXD, EXACT>(p, (float)e, a.mco, a.mthr, base >> 5);
+        if ((unsigned)(c - base) < 32u) m &= ~(1u << (c - base));
+        continue;
+      }
+      const int cc = base + __builtin_ctz(m);
+      const CP<ChanHead<T>> h = chan_at(a, cc);
+      const T r = chan_r_of<T, MAXD>(h, d, p);
+      const bool counts = term_counts<T, true>(h, r, gg);
+      const uint64_t lanes = __ballot(counts);
+      if (pend.nq + __popcll(lanes) > 64) break;  // run the queue, then this channel again
+      m &= m - 1;
+      f += h->twin * r;
+      if (lanes) pend.push(cc, lanes, counts, r);
+    }
+    pend.run(a, d, M, mshift, p, gg);
+  } while (!last);
+  CP<PeakDim<T>> pmap = cp(a.pmap);
+  CP<T> pnorm = cp(a.pnorm);
+  CP<int32_t> orphans = cp(a.orphans);
   for (int o = 0; o < a.n_orphan; ++o) {
     const int i2 = orphans[o];
     f += pnorm[i2] * peak_r<T, MAXD>(pmap + (size_t)i2 * d, d, p);
@@ -381,6 +582,11 @@ __device__ __forceinline__ void other_terms(const SampleArgs<T>& a, int c, int d
 // x-space table and its per-bin sums of w^2 live in LDS.
 // ---------------------------------------------------------------------------
 
+// Pair channels (ChanHead) take their own path in the FP64 batched pass, whose
+// small units wait for one read after another.
+template <typename T, int MAXD, int BLOCK>
+constexpr bool kPairPath = sizeof(T) == 8 && BLOCK == 0 && MAXD <= 16;
+
 // One work unit of a pass: unit g of the job's G units takes the calls
 // [g N/G, (g+1) N/G).  BLOCK > 0: the workgroup size as a constant, else
 // blockDim.x.  EXACT: the job's dimension is MAXD (no per-axis guards).
@@ -388,30 +594,32 @@ __device__ __forceinline__ void other_terms(const SampleArgs<T>& a, int c, int d
 // zero terms are skipped); the results are the same either way.  TRACE:
 // also write f, g and w of the calls in the argument record's trace window
 // (the same code path otherwise).  MT > 0: the job's hint cells per axis as
-// a constant (its offsets fold into immediates).  Every thread of the
-// workgroup calls it with the same unit.
+// a constant (its offsets fold into immediates).  MASK: channels left out
+// by masks (mcv_mask.h).  Every thread of the workgroup
+// calls it
+// with the same unit.  staged: the channel whose own table the workgroup holds
+// in LDS (-1: none, and the sums are not yet cleared).
 template <typename T, int MAXD, int BLOCK, bool EXACT, bool TB, bool TRACE = false, int RNG = 0,
-          int MT = 0, bool LAZY = false, bool REFINED = false>
+          int MT = 0, bool LAZY = false, bool MASK = false>
 __device__ __forceinline__ void sample_unit(const SampleArgs<T>& a, int g, int G, uint32_t tag,
-                                            unsigned char* smem) {
+                                            unsigned char* smem, int& staged) {
   static_assert(RNG == 0 || (BLOCK > 0 && (BLOCK & (BLOCK - 1)) == 0),
                 "MRG32k3a substreams advance by a power-of-two workgroup");
-  constexpr int GROUP = sizeof(T) == 4 ? 5 : 2;
+  constexpr int GROUP = sizeof(T) == 4 ? 5 : BLOCK > 0 ? 2 : 4;
   const int block = BLOCK > 0 ? BLOCK : (int)blockDim.x;
   const int waves = block >> 6;
   Pair<T>* ownT = reinterpret_cast<Pair<T>*>(smem + a.off_own);
   double* hist = reinterpret_cast<double*>(smem + a.off_hist);
   double* red = reinterpret_cast<double*>(smem + a.off_red);
+  // this wavefront's lookup queue, behind the cross-wave reduction
+  WaveQueue<T>* queue = reinterpret_cast<WaveQueue<T>*>(smem + a.off_queue) + (threadIdx.x >> 6);
 
   const int d = EXACT ? MAXD : a.d, n = a.n, K = a.K;
   const int tid = threadIdx.x;
   CP<int64_t> start = cp(a.start);
   CP<double> alpha = cp(a.alpha);
   CP<DimMap<T>> cmap = cp(a.cmap);
-  CP<ChanType> ctype = cp(a.ctype);
   CP<T> cnorm = cp(a.cnorm);
-  CP<T> twin = cp(a.twin_pn);
-  CP<T> gab = cp(a.gab);
 
   const int64_t ntot = start[K];
   const int64_t lo = (int64_t)g * ntot / G;
@@ -424,7 +632,8 @@ __device__ __forceinline__ void sample_unit(const SampleArgs<T>& a, int g, int G
   const int mshift = MT > 0 ? (MT == 512 ? 18 : 19) : a.mshift;
   const int chT = d * sT;  // entries per channel table
 
-  for (int t = tid; t < dn; t += block) hist[t] = 0.0;
+  if (staged < 0)
+    for (int t = tid; t < dn; t += block) hist[t] = 0.0;
 
   int c = 0;
   while (c < K - 1 && start[c + 1] <= lo) ++c;
@@ -432,8 +641,11 @@ __device__ __forceinline__ void sample_unit(const SampleArgs<T>& a, int g, int G
     const int64_t s0 = start[c] > lo ? start[c] : lo;
     const int64_t s1 = start[c + 1] < hi ? start[c + 1] : hi;
     __syncthreads();
-    copy16(ownT, a.xtab + (size_t)c * chT, chT * (int)sizeof(Pair<T>), block);
-    __syncthreads();
+    if (staged != c) {  // uniform
+      copy16(ownT, a.xtab + (size_t)c * chT, chT * (int)sizeof(Pair<T>), block);
+      staged = c;
+      __syncthreads();
+    }
 
     // Per-lane sums of w and w^2 of the segment: plain FP64 sums over at
     // most kFold rounds, folded into compensated sums (little state live
@@ -447,9 +659,11 @@ __device__ __forceinline__ void sample_unit(const SampleArgs<T>& a, int g, int G
     const T al_c = (T)alpha[c];
     CP<DimMap<T>> cm_c = cmap + (size_t)c * d;
     const T own_norm = al_c * cnorm[c];
-    const int iso_c = ctype[c].iso;
-    const uint32_t gm_c = ctype[c].gmask, bm_c = ctype[c].bmask;
-    const T tw_c = twin[c];
+    const CP<ChanHead<T>> h_c = chan_at(a, c);
+    // grouped axis maps in the single-job pass only: the batched kernel's 13
+    // bodies would each carry both paths (its FP64 pass 2.77 -> 2.95 ms)
+    const bool all_gauss = (h_c->kind & kChanLin) != 0;
+    const T tw_c = h_c->twin;
     // MRG32k3a: this lane's first call of the segment is substream
     // s0 + tid - start[c] of channel c's stream; each round moves BLOCK
     // substreams on
@@ -463,7 +677,9 @@ __device__ __forceinline__ void sample_unit(const SampleArgs<T>& a, int g, int G
       T p[MAXD];
       uint32_t jp[(MAXD + 3) / 4];
       T f = T(0), gg = T(1);
-      if (valid) {
+      // with masks every lane of a wavefront that holds a call takes part; a
+      // lane beyond the segment evaluates a point that is not counted
+      if (MASK ? base + (tid & ~63) < s1 : valid) {
         uint32_t u[MAXD];
         if constexpr (RNG == 1) {
           Mrg w = mst;
@@ -473,11 +689,15 @@ __device__ __forceinline__ void sample_unit(const SampleArgs<T>& a, int g, int G
         } else {
           draw_words<MAXD>(a.seed, (uint64_t)i, tag, d, u);
         }
-        const T own = forward_point<T, MAXD, REFINED>(u, d, n, cm_c, ownT, sT, p, jp);
-        const T r_c = chan_r<T, MAXD>(gab + (size_t)c * 2 * d, iso_c, gm_c, bm_c, d, p);
+        const T own = forward_point<T, MAXD, (BLOCK > 0)>(u, d, n, cm_c, ownT, sT, all_gauss, p, jp);
+        const T r_c = chan_r_of<T, MAXD>(h_c, d, p);
         f = tw_c * r_c;
         gg = own_norm * own * r_c;
-        other_terms<T, MAXD, GROUP, EXACT, TB, LAZY>(a, c, d, M, mshift, p, f, gg);
+        if constexpr (MASK)
+          masked_terms<T, MAXD, GROUP, EXACT>(a, c, d, M, mshift, queue, p, f, gg);
+        else
+          other_terms<T, MAXD, GROUP, EXACT, TB, LAZY, kPairPath<T, MAXD, BLOCK>>(a, c, d, M, mshift,
+                                                                                 p, f, gg);
       }
       // ---- weights and sums (FP64)
       if (valid) {
@@ -612,12 +832,13 @@ constexpr int kQueues = 8;
 template <typename T, int MAXD, bool TB>
 __device__ __forceinline__ void queue_unit(const SampleArgs<T>& a, int u, int G, uint32_t tag,
                                            unsigned char* smem) {
-#define MCV_EXACT_CASE(D)                                   \
-  case D:                                                   \
-    if constexpr (D <= MAXD) {                              \
-      sample_unit<T, D, 0, true, TB>(a, u, G, tag, smem);   \
-      return;                                               \
-    }                                                       \
+  int staged = -1;  // the unit's job may differ from the one before
+#define MCV_EXACT_CASE(D)                                         \
+  case D:                                                         \
+    if constexpr (D <= MAXD) {                                    \
+      sample_unit<T, D, 0, true, TB>(a, u, G, tag, smem, staged); \
+      return;                                                     \
+    }                                                             \
     break;
   switch (a.d) {
     MCV_EXACT_CASE(1)
@@ -636,7 +857,7 @@ __device__ __forceinline__ void queue_unit(const SampleArgs<T>& a, int u, int G,
       break;
   }
 #undef MCV_EXACT_CASE
-  if constexpr (MAXD > 12) sample_unit<T, MAXD, 0, false, TB>(a, u, G, tag, smem);
+  if constexpr (MAXD > 12) sample_unit<T, MAXD, 0, false, TB>(a, u, G, tag, smem, staged);
 }
 
 template <typename T, int MAXD, int LB, bool TB>
@@ -681,51 +902,51 @@ __global__ __launch_bounds__(LB, LB == 256 ? (sizeof(T) == 4 ? 6 : 4) : 1) void 
   }
 }
 
-// Launch shape of the single-job kernel per precision (measured best on the
-// d = 10, 32-channel, 100-bin workload):
-// 256-thread workgroups with the registers capped for 7 (FP32) or 4 (FP64)
-// waves per SIMD (a few spills, more latency hidden; FP32 at 5, 6, 7 and 8
-// waves: 6.45, 6.00, 5.62 and 5.75 ms).  With MRG32k3a streams (more state
-// per lane) 6 was faster with one co-resident set of workgroups (6.85 ms
-// against 7.05 at 7), 7 with up to 8 sets (5.24 against 5.31).
+// Launch shape of the single-job kernel: 256-thread workgroups, registers
+// capped for a number of waves per SIMD (d = 10, 32 channels, 24 Gaussian and
+// 8 Breit-Wigner: FP32 with masks 4.10, 3.93 and 4.36 ms a pass of 1e8 at 4, 5
+// and 6 waves; FP64 2.08, 1.96 and 2.4 ms a pass of 1e7 at 3, 4 and 5; FP32
+// without masks 7, where its few registers allow it).
 template <typename T>
-struct Tune;
-template <>
-struct Tune<float> {
-  static constexpr int BLOCK = 256, PPT = 1, MIN_WAVES = 7, MIN_WAVES_MRG = 7;
+struct Tune {
+  static constexpr int BLOCK = 256, PPT = 1;
 };
-template <>
-struct Tune<double> {
-  static constexpr int BLOCK = 256, PPT = 1, MIN_WAVES = 4, MIN_WAVES_MRG = 4;
-};
-template <typename T, int RNG>
-constexpr int kMinWaves = RNG == 1 ? Tune<T>::MIN_WAVES_MRG : Tune<T>::MIN_WAVES;
+template <typename T, bool MASK>
+constexpr int kMinWaves = sizeof(T) == 4 ? (MASK ? 5 : 7) : 4;
 
-// Single-job pass: workgroup g of the grid is unit g.  RNG: 0 Philox words,
-// 1 MRG32k3a streams.  Lazy walks in FP32 only (d = 10, 32 channels: FP32
-// 6.16 -> 5.91 ms with them, FP64 22.4 -> 23.1 ms; the batched pass, whose
-// channels all use the log map, 69 -> 76 ms, so it does without).
+// Single-job pass: as many workgroups as fit the chip at once drain the
+// pass's units in order, each taking the next one when it is done, so that
+// units of unequal cost (the channels' calls differ by an order of magnitude)
+// leave no tail longer than a unit; consecutive units mostly share a channel,
+// whose own table then stays in LDS.  A unit's results do not depend on which
+// workgroup runs it.  The counter is cleared by the allocation before.  RNG: 0
+// Philox words, 1 MRG32k3a streams.  Lazy walks in FP32 only (d = 10, 32
+// channels: FP32 6.16 -> 5.91 ms with them, FP64 22.4 -> 23.1 ms; the batched
+// pass, whose channels all use the log map, 69 -> 76 ms, so it does without).
+// TRACE: the same with its trace window written (the tag then comes from the
+// argument record).
 template <typename T>
 constexpr bool kLazyWalks = sizeof(T) == 4;
 
-template <typename T, int MAXD, int PPT, int BLOCK, bool EXACT, int RNG = 0, int MT = 0>
-__global__ __launch_bounds__(BLOCK, (kMinWaves<T, RNG>)) void k_sample(SampleArgs<T> a) {
+template <typename T, int MAXD, int PPT, int BLOCK, bool EXACT, int RNG = 0, int MT = 0,
+          bool MASK = false, bool TRACE = false>
+__global__ __launch_bounds__(BLOCK, (kMinWaves<T, MASK>)) void k_sample(SampleArgs<T> a) {
   static_assert(PPT == 1, "one call per thread and round");
   extern __shared__ __align__(16) unsigned char smem[];
-  const uint32_t tag = (uint32_t)cp(a.iter)[0];
-  sample_unit<T, MAXD, BLOCK, EXACT, true, false, RNG, MT, kLazyWalks<T>, true>(
-      a, blockIdx.x, gridDim.x, tag, smem);
+  __shared__ int next_s;
+  const uint32_t tag = TRACE ? a.tag : (uint32_t)cp(a.iter)[0];
+  int staged = -1;
+  for (int u = blockIdx.x; u < a.units;) {
+    int next = 0;
+    if (threadIdx.x == 0) next = atomicAdd(a.next, 1);  // under way while the unit runs
+    sample_unit<T, MAXD, BLOCK, EXACT, true, TRACE, RNG, MT, kLazyWalks<T>, MASK>(
+        a, u, a.units, tag, smem, staged);
+    if (threadIdx.x == 0) next_s = next + (int)gridDim.x;
+    __syncthreads();
+    u = __builtin_amdgcn_readfirstlane(next_s);
+    __syncthreads();
+  }
 }
-
-// The single-job pass with its trace window written (k_sample's code path,
-// launch bounds and grid; the iteration tag comes from the argument record).
-template <typename T, int MAXD, int PPT, int BLOCK, bool EXACT, int RNG = 0, int MT = 0>
-__global__ __launch_bounds__(BLOCK, (kMinWaves<T, RNG>)) void k_sample_trace(SampleArgs<T> a) {
-  extern __shared__ __align__(16) unsigned char smem[];
-  sample_unit<T, MAXD, BLOCK, EXACT, true, true, RNG, MT, kLazyWalks<T>, true>(
-      a, blockIdx.x, gridDim.x, a.tag, smem);
-}
-
 
 // ---------------------------------------------------------------------------
 // Host side: argument records, LDS layouts and launch shapes.
@@ -743,32 +964,31 @@ SampleArgs<T> make_args(const JobDev& j, uint32_t tag) {
   a.tag = tag;
   a.seed = j.seed;
   a.iter = j.iter_dev;
+  a.next = j.next;
   a.start = j.start;
   a.alpha = j.alpha;
-  a.ctype = j.ctype;
   a.orphans = j.orphans;
   a.n_orphan = j.n_orphan;
   if (sizeof(T) == 8) {
     a.cmap = reinterpret_cast<const DimMap<T>*>(j.cmap64);
     a.cnorm = reinterpret_cast<const T*>(j.cnorm64);
-    a.twin_pn = reinterpret_cast<const T*>(j.twin_pn64);
     a.pmap = reinterpret_cast<const PeakDim<T>*>(j.pmap64);
     a.pnorm = reinterpret_cast<const T*>(j.pnorm64);
   } else {
     a.cmap = reinterpret_cast<const DimMap<T>*>(j.cmap32);
     a.cnorm = reinterpret_cast<const T*>(j.cnorm32);
-    a.twin_pn = reinterpret_cast<const T*>(j.twin_pn32);
     a.pmap = reinterpret_cast<const PeakDim<T>*>(j.pmap32);
     a.pnorm = reinterpret_cast<const T*>(j.pnorm32);
   }
   a.xtab = reinterpret_cast<const Pair<T>*>(j.xtab);
   a.ptab = reinterpret_cast<const Pair<T>*>(j.ptab);
   a.ctab = reinterpret_cast<const Cell<T>*>(j.ctab);
-  a.gbound = reinterpret_cast<const T*>(j.gbound);
-  a.aterm = reinterpret_cast<const T*>(j.aterm);
-  a.gab = reinterpret_cast<const T*>(j.gab);
+  a.crec = j.crec;
+  a.cstride = chan_stride<T>(j.d);
   a.hab = j.hab;
-  a.skx = j.skx;
+  a.mco = j.mco;
+  a.mthr = j.mthr;
+  a.fpos = j.fpos;
   a.part = j.part;
   a.hpart = j.hpart;
   a.rng = j.rng;
@@ -787,7 +1007,7 @@ static inline int align16(int x) { return (x + 15) & ~15; }
 // x-space table, the per-bin sums of w^2 and the cross-wave reduction.
 // Returns the end of the layout (bytes used, base included).
 template <typename T>
-int lds_layout(SampleArgs<T>& a, int waves, int base = 0) {
+int lds_layout(SampleArgs<T>& a, int waves, int base = 0, bool masked = false) {
   const int chT = a.d * a.sT * (int)sizeof(Pair<T>);
   int off = base;
   a.off_own = off;
@@ -796,118 +1016,125 @@ int lds_layout(SampleArgs<T>& a, int waves, int base = 0) {
   off += align16(a.d * a.n * 8);
   a.off_red = off;
   off += align16(waves * 6 * 8);
+  a.off_queue = off;
+  if (masked) off += waves * (int)sizeof(WaveQueue<T>);
   return off;
 }
 
-// Workgroups of one pass: as many as are co-resident (per_cu per CU) and no
-// more than leave every workgroup a few rounds; with oversub, up to oversub
-// times the co-resident count where every workgroup still gets 32 rounds
-// (the hardware starts the later ones as earlier ones finish); at most the
-// partial buffers' units.
-int grid_for(const JobDev& j, int per_cu, int per_round, int64_t n_points, int oversub = 1) {
-  if (per_cu < 1) per_cu = 1;
-  int64_t G = (int64_t)j.n_cu * per_cu;
-  const int64_t want = (n_points + 4 * (int64_t)per_round - 1) / (4 * (int64_t)per_round);
-  if (want < G) G = want > 0 ? want : 1;
-  if (oversub > 1) {
-    int64_t more = (int64_t)j.n_cu * per_cu * oversub;
-    const int64_t full = n_points / (32 * (int64_t)per_round);
-    if (full < more) more = full;
-    if (more > G) G = more;
+// Work units of one pass of n_points calls in rounds of per_round, for G
+// workgroups that fit the chip at once.  A unit of r rounds costs r rounds and
+// its start and end (its table, its record and bins written and summed: about
+// one and a half); the workgroups run ceil(U / G) units each one after the other,
+// and end about half a unit apart.  The least of ceil(U / G) (r + 3/2) + r / 2:
+// for a long pass r grows as sqrt(R / G), R the pass's rounds, for a short one
+// the units come out at or just under whole multiples of G.  Measured best
+// (d = 10, 32 channels): r = 1 (R = 40), 2 to 3 (1300), 2 and 4 but not 3 (3900,
+// G = 1024: 1302 units ran as two sets, 1.46 -> 1.60 ms for ten passes), 6 to
+// 16 (39000), flat from 8 to 48 (390000).  At most the partial buffers' units.
+inline int units_for(const JobDev& j, int per_round, int64_t n_points, int64_t G) {
+  const int64_t R = (n_points + per_round - 1) / per_round;
+  if (G < 1) G = 1;
+  int64_t best = 1;
+  double least = INFINITY;
+  for (int64_t r = 1; r <= 4096 && (r == 1 || (r - 1) * G < R); ++r) {
+    const int64_t U = (R + r - 1) / r;
+    if (U > j.gmax) continue;
+    const double t = (double)((U + G - 1) / G) * ((double)r + 1.5) + 0.5 * (double)r;
+    if (t < least) {
+      least = t;
+      best = U;
+    }
   }
-  if (G > j.gmax) G = j.gmax;
-  return (int)G;
+  if (least == INFINITY) best = j.gmax;
+  return (int)(best < 1 ? 1 : best);
 }
 
-constexpr int kOversub = 8;
-
-// Workgroups of k_sample for a pass of n_points (kOversub times its
-// occupancy), or -1 if the kernel cannot get its LDS.
-template <typename T, int MAXD, bool EXACT, int RNG, int MT>
-int sample_grid_m(const JobDev& j, int64_t n_points) {
+// Work units and workgroups of k_sample for a pass of n_points.
+template <typename T, int MAXD, bool EXACT, int RNG, int MT, bool MASK, bool TRACE = false>
+Split sample_split_m(const JobDev& j, int64_t n_points) {
   constexpr int BLOCK = Tune<T>::BLOCK, PPT = Tune<T>::PPT;
   SampleArgs<T> a = make_args<T>(j, 0);
-  const int lds = lds_layout<T>(a, BLOCK / 64);
-  auto kern = k_sample<T, MAXD, PPT, BLOCK, EXACT, RNG, MT>;
+  const int lds = lds_layout<T>(a, BLOCK / 64, 0, MASK);
+  auto kern = k_sample<T, MAXD, PPT, BLOCK, EXACT, RNG, MT, MASK, TRACE>;
   if (lds > 64 * 1024 &&
       hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds) !=
           hipSuccess)
-    return -1;
+    return Split{0, 0};
   int per_cu = 0;
   if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void*)kern, BLOCK, lds) !=
-      hipSuccess)
-    return -1;
-  // Units of unequal cost (the channels' calls differ by an order of
-  // magnitude in cost) finish unevenly: with up to 8 workgroups per resident
-  // slot the late ones overlap the tail.  d = 10, 32 channels, FP32: 1, 2, 4,
-  // 8 and 16 times the resident count took 5.57, 5.10, 4.56, 4.37 and 4.41
-  // ms (1e8 calls: 8 times is 27 rounds per workgroup; the 32-round floor
-  // keeps 6.8 times).
-  return grid_for(j, per_cu, BLOCK * PPT, n_points, kOversub);
+          hipSuccess ||
+      per_cu < 1)
+    return Split{0, 0};
+  const int G = per_cu * j.n_cu;
+  Split sp{units_for(j, BLOCK * PPT, n_points, G), G};
+  if (sp.G > sp.U) sp.G = sp.U;
+  return sp;
 }
 
-template <typename T, int MAXD, bool EXACT, int RNG, int MT>
-int launch_sample_m(const JobDev& j, int64_t n_points, hipStream_t s) {
+template <typename T, int MAXD, bool EXACT, int RNG, int MT, bool MASK>
+Split launch_sample_m(const JobDev& j, int64_t n_points, hipStream_t s) {
   constexpr int BLOCK = Tune<T>::BLOCK, PPT = Tune<T>::PPT;
-  const int G = sample_grid_m<T, MAXD, EXACT, RNG, MT>(j, n_points);
-  if (G < 1) return -1;
+  const Split sp = sample_split_m<T, MAXD, EXACT, RNG, MT, MASK>(j, n_points);
+  if (sp.G < 1) return sp;
   SampleArgs<T> a = make_args<T>(j, 0);
-  const int lds = lds_layout<T>(a, BLOCK / 64);
-  hipLaunchKernelGGL((k_sample<T, MAXD, PPT, BLOCK, EXACT, RNG, MT>), dim3(G), dim3(BLOCK), lds, s,
-                     a);
-  return G;
+  a.units = sp.U;
+  const int lds = lds_layout<T>(a, BLOCK / 64, 0, MASK);
+  hipLaunchKernelGGL((k_sample<T, MAXD, PPT, BLOCK, EXACT, RNG, MT, MASK>), dim3(sp.G),
+                     dim3(BLOCK), lds, s, a);
+  return sp;
 }
 
-// The trace instantiation over the trace allocation (t_start, t_alpha) with
-// G workgroups (k_sample's grid for the same pass).
-template <typename T, int MAXD, bool EXACT, int RNG, int MT>
-int launch_sample_trace_m(const JobDev& j, int G, uint32_t tag, int64_t first, int64_t count,
-                          double* out, hipStream_t s) {
+// The trace instantiation over the trace allocation (t_start, t_alpha), split
+// as k_sample splits a pass of n_points.
+template <typename T, int MAXD, bool EXACT, int RNG, int MT, bool MASK>
+Split launch_sample_trace_m(const JobDev& j, int64_t n_points, uint32_t tag, int64_t first,
+                            int64_t count, double* out, hipStream_t s) {
   constexpr int BLOCK = Tune<T>::BLOCK, PPT = Tune<T>::PPT;
+  Split sp = sample_split_m<T, MAXD, EXACT, RNG, MT, MASK, true>(j, n_points);
+  if (sp.G < 1) return sp;
   SampleArgs<T> a = make_args<T>(j, tag);
+  a.units = sp.U;
   a.start = j.t_start;
   a.alpha = j.t_alpha;
-  a.aterm = reinterpret_cast<const T*>(j.t_aterm);
+  a.crec = j.t_crec;
   a.tr_first = first;
   a.tr_count = count;
   a.tr_out = out;
-  const int lds = lds_layout<T>(a, BLOCK / 64);
-  auto kern = k_sample_trace<T, MAXD, PPT, BLOCK, EXACT, RNG, MT>;
-  if (lds > 64 * 1024 &&
-      hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds) !=
-          hipSuccess)
-    return -1;
-  hipLaunchKernelGGL(kern, dim3(G), dim3(BLOCK), lds, s, a);
-  return G;
+  const int lds = lds_layout<T>(a, BLOCK / 64, 0, MASK);
+  hipLaunchKernelGGL((k_sample<T, MAXD, PPT, BLOCK, EXACT, RNG, MT, MASK, true>), dim3(sp.G),
+                     dim3(BLOCK), lds, s, a);
+  return sp;
 }
 
-// The single-job pass with Philox words takes the job's hint cells per axis
-// as a constant (256 or 512); MRG32k3a passes read it from the arguments.
+// Calls FN<T, MAXD, EXACT, RNG, MT, MASK>(...).  The single-job pass with
+// Philox words takes the job's hint cells per axis as a constant (256 or
+// 512); MRG32k3a passes read it from the arguments.  MASK where the job has
+// mask coefficients.
+#define MCV_SAMPLE_VARIANT(FN, ...)                                                     \
+  do {                                                                                  \
+    constexpr bool kMask = sizeof(T) == 4 && mask_form(MAXD, EXACT).steps > 0;                           \
+    if constexpr (RNG == 0) {                                                           \
+      if (kMask && j.masked)                                                            \
+        return j.M == 512 ? FN<T, MAXD, EXACT, RNG, 512, kMask>(__VA_ARGS__)            \
+                          : FN<T, MAXD, EXACT, RNG, 256, kMask>(__VA_ARGS__);           \
+      return j.M == 512 ? FN<T, MAXD, EXACT, RNG, 512, false>(__VA_ARGS__)              \
+                        : FN<T, MAXD, EXACT, RNG, 256, false>(__VA_ARGS__);             \
+    }                                                                                   \
+    if (kMask && j.masked) return FN<T, MAXD, EXACT, RNG, 0, kMask>(__VA_ARGS__);       \
+    return FN<T, MAXD, EXACT, RNG, 0, false>(__VA_ARGS__);                              \
+  } while (0)
+
 template <typename T, int MAXD, bool EXACT, int RNG = 0>
-int sample_grid_t(const JobDev& j, int64_t n_points) {
-  if constexpr (RNG == 0)
-    return j.M == 512 ? sample_grid_m<T, MAXD, EXACT, RNG, 512>(j, n_points)
-                      : sample_grid_m<T, MAXD, EXACT, RNG, 256>(j, n_points);
-  return sample_grid_m<T, MAXD, EXACT, RNG, 0>(j, n_points);
+Split launch_sample_t(const JobDev& j, int64_t n_points, hipStream_t s) {
+  MCV_SAMPLE_VARIANT(launch_sample_m, j, n_points, s);
 }
 
 template <typename T, int MAXD, bool EXACT, int RNG = 0>
-int launch_sample_t(const JobDev& j, int64_t n_points, hipStream_t s) {
-  if constexpr (RNG == 0)
-    return j.M == 512 ? launch_sample_m<T, MAXD, EXACT, RNG, 512>(j, n_points, s)
-                      : launch_sample_m<T, MAXD, EXACT, RNG, 256>(j, n_points, s);
-  return launch_sample_m<T, MAXD, EXACT, RNG, 0>(j, n_points, s);
+Split launch_sample_trace_t(const JobDev& j, int64_t n_points, uint32_t tag, int64_t first,
+                            int64_t count, double* out, hipStream_t s) {
+  MCV_SAMPLE_VARIANT(launch_sample_trace_m, j, n_points, tag, first, count, out, s);
 }
-
-template <typename T, int MAXD, bool EXACT, int RNG = 0>
-int launch_sample_trace_t(const JobDev& j, int G, uint32_t tag, int64_t first, int64_t count,
-                          double* out, hipStream_t s) {
-  if constexpr (RNG == 0)
-    return j.M == 512
-               ? launch_sample_trace_m<T, MAXD, EXACT, RNG, 512>(j, G, tag, first, count, out, s)
-               : launch_sample_trace_m<T, MAXD, EXACT, RNG, 256>(j, G, tag, first, count, out, s);
-  return launch_sample_trace_m<T, MAXD, EXACT, RNG, 0>(j, G, tag, first, count, out, s);
-}
+#undef MCV_SAMPLE_VARIANT
 
 
 }  // namespace

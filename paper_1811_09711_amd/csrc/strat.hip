@@ -51,10 +51,7 @@ __global__ __launch_bounds__(kStratBlock, kStratMinWaves<T>) void k_sample_strat
   const int sT = a.sT, chT = d * sT;
   CP<double> alpha = cp(a.alpha);
   CP<DimMap<T>> cmap = cp(a.cmap);
-  CP<ChanType> ctype = cp(a.ctype);
   CP<T> cnorm = cp(a.cnorm);
-  CP<T> twin = cp(a.twin_pn);
-  CP<T> gab = cp(a.gab);
   const int g = blockIdx.x, G = gridDim.x;
   CP<int64_t> start = cp(a.start);
   CP<int64_t> bstart = cp(a.bstart);
@@ -75,9 +72,9 @@ __global__ __launch_bounds__(kStratBlock, kStratMinWaves<T>) void k_sample_strat
     __syncthreads();
     CP<DimMap<T>> cm_c = cmap + (size_t)c * d;
     const T own_norm = (T)alpha[c] * cnorm[c];
-    const int iso_c = ctype[c].iso;
-    const uint32_t gm_c = ctype[c].gmask, bm_c = ctype[c].bmask;
-    const T tw_c = twin[c];
+    const CP<ChanHead<T>> h_c = chan_at(a, c);
+    const T tw_c = h_c->twin;
+    const bool all_gauss = (h_c->kind & kChanLin) != 0;
     const bool small_boxes = bstart[c + 1] - bstart[c] <= (int64_t)0xFFFFFFFF;
     Neu S1{0.0, 0.0}, S2{0.0, 0.0}, SW{0.0, 0.0};
     double wmax = 0.0, nbad = 0.0;
@@ -127,8 +124,8 @@ __global__ __launch_bounds__(kStratBlock, kStratMinWaves<T>) void k_sample_strat
         }
         T p[MAXD];
         uint32_t jpk[(MAXD + 3) / 4];
-        const T own = forward_point_jf<T, MAXD>(jj, fr, d, cm_c, ownT, sT, p, jpk);
-        const T r_c = chan_r<T, MAXD>(gab + (size_t)c * 2 * d, iso_c, gm_c, bm_c, d, p);
+        const T own = forward_point_jf<T, MAXD, true>(jj, fr, d, cm_c, ownT, sT, all_gauss, p, jpk);
+        const T r_c = chan_r_of<T, MAXD>(h_c, d, p);
         T f = tw_c * r_c, gg = own_norm * own * r_c;
         other_terms<T, MAXD, GROUP, false, true, kLazyWalks<T>>(a, c, d, a.M, a.mshift, p, f, gg);
         const T wt = f / gg;
@@ -206,7 +203,7 @@ __global__ __launch_bounds__(kStratBlock, kStratMinWaves<T>) void k_sample_strat
 }
 
 template <typename T, int MAXD>
-int launch_t(const JobDev& j, int64_t n_points, hipStream_t s) {
+Split launch_t(const JobDev& j, int64_t n_points, hipStream_t s) {
   SampleArgs<T> a = make_args<T>(j, 0);
   // LDS: the segment's x-space table, the per-bin sums and the cross-wave
   // reduction (8 values per wave)
@@ -218,21 +215,20 @@ int launch_t(const JobDev& j, int64_t n_points, hipStream_t s) {
   if (lds > 64 * 1024 &&
       hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds) !=
           hipSuccess)
-    return -1;
+    return Split{0, 0};
   int per_cu = 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void*)kern, kStratBlock,
-                                                   lds) != hipSuccess)
-    return -1;
-  // about n_points / strat boxes: a few rounds of boxes per workgroup, and
-  // as in the importance pass up to kOversub times the co-resident count
-  const int G =
-      grid_for(j, per_cu, kStratBlock * (j.strat > 0 ? j.strat : 1), n_points, kOversub);
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void*)kern, kStratBlock, lds) !=
+      hipSuccess)
+    return Split{0, 0};
+  // about n_points / strat boxes, one per lane and round; a workgroup per unit
+  const int G = units_for(j, kStratBlock * (j.strat > 0 ? j.strat : 1), n_points,
+                          (int64_t)per_cu * j.n_cu);
   hipLaunchKernelGGL(kern, dim3(G), dim3(kStratBlock), lds, s, a);
-  return G;
+  return Split{G, G};
 }
 
 template <typename T>
-int launch_p(const JobDev& j, int64_t n, hipStream_t s) {
+Split launch_p(const JobDev& j, int64_t n, hipStream_t s) {
   const int d = j.d;
   if (d <= 2) return launch_t<T, 2>(j, n, s);
   if (d <= 4) return launch_t<T, 4>(j, n, s);
@@ -246,7 +242,7 @@ int launch_p(const JobDev& j, int64_t n, hipStream_t s) {
 
 }  // namespace
 
-int launch_sample_strat(const JobDev& j, int64_t n_points, hipStream_t s) {
+Split launch_sample_strat(const JobDev& j, int64_t n_points, hipStream_t s) {
   return j.prec == 1 ? launch_p<float>(j, n_points, s) : launch_p<double>(j, n_points, s);
 }
 
