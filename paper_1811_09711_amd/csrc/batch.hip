@@ -273,15 +273,15 @@ mcv_status Engine::history(int index, double* out, int cap, int* n_iter) {
   if (index < 0 || index >= (int)jobs.size() || !jobs[index].live)
     return fail(MCV_E_INVALID, "no such job");
   const Job& jb = jobs[index];
-  MCV_HIP(hipStreamSynchronize(stream));
+  // the device's count of passes, and the rows that the host has started
+  const int m = cap < jb.iters ? cap : jb.iters;
   int32_t it = 0;
-  MCV_HIP(hipMemcpy(&it, jb.j.iter_dev, sizeof it, hipMemcpyDeviceToHost));
-  if (n_iter) *n_iter = it;
-  const int m = cap < it ? cap : it;
-  if (out && m > 0)
-    MCV_HIP(hipMemcpy(out, jb.j.history, (size_t)m * kHistStride * sizeof(double),
-                      hipMemcpyDeviceToHost));
-  return MCV_OK;
+  const HostSeg seg[2] = {
+      {&it, jb.j.iter_dev, sizeof it},
+      {m > 0 ? out : nullptr, jb.j.history, (size_t)m * kHistStride * sizeof(double)}};
+  const mcv_status st = rd.read(seg, 2, stream);
+  if (st == MCV_OK && n_iter) *n_iter = it;
+  return st;
 }
 
 }  // namespace mcv
@@ -446,6 +446,11 @@ mcv_status mcv_batch_create(const mcv_problem* problems, const int64_t* n_points
     members.push_back(idx);
   }
   if (st == MCV_OK) st = e.build_set(members);
+  if (st == MCV_OK) {
+    size_t rb = mcv::kReadSmall;
+    for (const mcv::Job& jb : e.jobs) rb = std::max(rb, mcv::state_read_bytes(jb.j));
+    e.rd.reserve(rb);
+  }
   if (st != MCV_OK) {
     for (size_t i = 0; i < e.jobs.size(); ++i) e.remove_job((int)i);
     delete b;
@@ -478,12 +483,12 @@ mcv_status mcv_batch_get_history(mcv_batch* b, int32_t job, double* host_out, in
 mcv_status mcv_batch_result(mcv_batch* b, int32_t job, int32_t first, mcv_summary* out) {
   if (!b || !out) return fail(MCV_E_INVALID, "NULL argument");
   int n = 0;
-  mcv_status st = b->e.history(job, nullptr, 0, &n);
+  const int cap = job >= 0 && job < (int)b->e.jobs.size() ? b->e.jobs[job].iters : 0;
+  std::vector<double> h((size_t)cap * mcv::kHistStride);
+  mcv_status st = b->e.history(job, h.data(), cap, &n);
   if (st != MCV_OK) return st;
+  if (n > cap) n = cap;
   if (n == 0 || first < 0 || first >= n) return fail(MCV_E_STATE, "first_iter is not a completed iteration");
-  std::vector<double> h((size_t)n * mcv::kHistStride);
-  st = b->e.history(job, h.data(), n, &n);
-  if (st != MCV_OK) return st;
   mcv::combine_history(h.data(), n, first, out);
   return MCV_OK;
 }
@@ -494,17 +499,9 @@ mcv_status mcv_batch_get_state(mcv_batch* b, int32_t job, double* edges, double*
   mcv::Engine& e = b->e;
   if (job < 0 || job >= (int)e.jobs.size() || !e.jobs[job].live)
     return fail(MCV_E_INVALID, "no such job");
-  const JobDev& j = e.jobs[job].j;
-  MCV_HIP(hipStreamSynchronize(e.stream));
-  if (edges)
-    MCV_HIP(hipMemcpy(edges, j.edges, (size_t)j.K * j.d * (j.n + 1) * sizeof(double),
-                      hipMemcpyDeviceToHost));
-  if (alpha) MCV_HIP(hipMemcpy(alpha, j.alpha, j.K * sizeof(double), hipMemcpyDeviceToHost));
-  if (alloc) {
-    MCV_HIP(hipMemcpy(alloc, j.nc, j.K * sizeof(int64_t), hipMemcpyDeviceToHost));
-    MCV_HIP(hipMemcpy(alloc + j.K, j.start + j.K, sizeof(int64_t), hipMemcpyDeviceToHost));
-  }
-  return MCV_OK;
+  mcv::HostSeg seg[4];
+  mcv::state_segs(e.jobs[job].j, edges, alpha, alloc, seg);
+  return e.rd.read(seg, 4, e.stream);
 }
 
 mcv_status mcv_batch_info(mcv_batch* b, int32_t* n_units, int32_t* workgroups, int32_t* lds_bytes,
@@ -527,6 +524,7 @@ void mcv_batch_destroy(mcv_batch* b) {
   if (!b) return;
   if (b->e.stream) hipStreamSynchronize(b->e.stream);
   for (size_t i = 0; i < b->e.jobs.size(); ++i) b->e.remove_job((int)i);
+  b->e.rd.release();
   delete b;
 }
 

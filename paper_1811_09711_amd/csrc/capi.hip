@@ -37,6 +37,7 @@ struct mcv_integrator {
   double wmax_unw = -1.0;    // running w_max of unweighting (-1: not started)
   int64_t trials_done = 0;
   std::vector<void*> bufs;   // unweighting work buffers
+  mcv::HostRead rd;          // reads of the state and the pass sums
   // unweighting work buffers (grown on demand)
   int64_t u_cap = 0;
   uint8_t* u_accept = nullptr;
@@ -67,6 +68,7 @@ static void release(mcv_integrator* h) {
   h->bufs.clear();
   mcv::dev_free(h->block);
   h->block = nullptr;
+  h->rd.release();
 }
 
 namespace {
@@ -201,7 +203,8 @@ mcv_status mcv_create_integrator(const mcv_problem* p, void* hip_stream, mcv_int
     mcv_destroy(h);
     return st;
   }
-
+  const size_t rb = mcv::state_read_bytes(h->j);
+  if (rb > mcv::kReadSmall) h->rd.reserve(rb);
   *out = h;
   return MCV_OK;
 }
@@ -323,18 +326,9 @@ mcv_status mcv_result(mcv_integrator* h, int32_t first, mcv_summary* out) {
 
 mcv_status mcv_get_state(mcv_integrator* h, double* edges, double* alpha, int64_t* alloc) {
   if (!h) return fail(MCV_E_INVALID, "integrator is NULL");
-  JobDev& j = h->j;
-  hipStream_t s = h->stream;
-  if (edges)
-    MCV_HIP(hipMemcpyAsync(edges, j.edges, (size_t)j.K * j.d * (j.n + 1) * sizeof(double),
-                           hipMemcpyDeviceToHost, s));
-  if (alpha) MCV_HIP(hipMemcpyAsync(alpha, j.alpha, j.K * sizeof(double), hipMemcpyDeviceToHost, s));
-  if (alloc) {
-    MCV_HIP(hipMemcpyAsync(alloc, j.nc, j.K * sizeof(int64_t), hipMemcpyDeviceToHost, s));
-    MCV_HIP(hipMemcpyAsync(alloc + j.K, j.start + j.K, sizeof(int64_t), hipMemcpyDeviceToHost, s));
-  }
-  MCV_HIP(hipStreamSynchronize(s));
-  return MCV_OK;
+  mcv::HostSeg seg[4];
+  mcv::state_segs(h->j, edges, alpha, alloc, seg);
+  return h->rd.read(seg, 4, h->stream);
 }
 
 mcv_status mcv_set_state_for_test(mcv_integrator* h, const double* edges, const double* alpha) {
@@ -375,19 +369,15 @@ mcv_status mcv_set_state_for_test(mcv_integrator* h, const double* edges, const 
 mcv_status mcv_get_pass_stats(mcv_integrator* h, double* hist, double* channel_stats) {
   if (!h) return fail(MCV_E_INVALID, "integrator is NULL");
   JobDev& j = h->j;
-  hipStream_t s = h->stream;
-  if (hist)
-    MCV_HIP(hipMemcpyAsync(hist, j.hist, (size_t)j.K * j.d * j.n * sizeof(double),
-                           hipMemcpyDeviceToHost, s));
-  if (channel_stats) {
-    std::vector<double> st((size_t)j.K * mcv::kStatStride);
-    MCV_HIP(hipMemcpyAsync(st.data(), j.chstats, st.size() * sizeof(double),
-                           hipMemcpyDeviceToHost, s));
-    MCV_HIP(hipStreamSynchronize(s));
+  std::vector<double> st(channel_stats ? (size_t)j.K * mcv::kStatStride : 0);
+  const mcv::HostSeg seg[2] = {
+      {hist, j.hist, (size_t)j.K * j.d * j.n * sizeof(double)},
+      {channel_stats ? st.data() : nullptr, j.chstats, st.size() * sizeof(double)}};
+  const mcv_status rc = h->rd.read(seg, 2, h->stream);
+  if (rc != MCV_OK) return rc;
+  if (channel_stats)
     for (int c = 0; c < j.K; ++c)
       for (int q = 0; q < 7; ++q) channel_stats[c * 7 + q] = st[(size_t)c * mcv::kStatStride + q];
-  }
-  MCV_HIP(hipStreamSynchronize(s));
   return MCV_OK;
 }
 

@@ -66,6 +66,7 @@ void carve_inputs(JobDev& j, Carve& c) {
 
 void carve_state(JobDev& j, Carve& c) {
   const size_t d = j.d, K = j.K, n = j.n, P = j.P, tsz = j.prec == 1 ? 4 : 8;
+  c.take(j.history, (size_t)j.max_iter * kHistStride);  // read with iter_dev, which is close before
   c.take(j.cmap64, K * d);
   c.take(j.cmap32, K * d);
   c.take(j.cnorm64, K);
@@ -75,7 +76,12 @@ void carve_state(JobDev& j, Carve& c) {
   c.take(j.pnorm64, P);
   c.take(j.pnorm32, P);
   c.take(j.ctype, K);
-  c.take(j.edges, K * d * (n + 1));
+  c.take(j.edges, K * d * (n + 1));  // to start: read together
+  c.take(j.alpha, K);
+  c.take(j.nc, K);
+  c.take(j.start, K + 1);
+  c.take(j.hist, K * d * n);  // and chstats: read together
+  c.take(j.chstats, K * kStatStride);
   char* xt = nullptr;
   char* pt = nullptr;
   c.take(xt, K * d * (size_t)j.sT * 2 * tsz);
@@ -99,9 +105,6 @@ void carve_state(JobDev& j, Carve& c) {
     c.take(j.moff, Kp * 2);
     c.take(j.mthr, Kp);
   }
-  c.take(j.alpha, K);
-  c.take(j.nc, K);
-  c.take(j.start, K + 1);
   c.take(j.t_alpha, K);
   c.take(j.t_nc, K);
   c.take(j.t_start, K + 1);
@@ -110,9 +113,6 @@ void carve_state(JobDev& j, Carve& c) {
   c.take(j.bstart, K + 1);
   c.take(j.t_nr, K);
   c.take(j.t_spb, K);
-  c.take(j.hist, K * d * n);
-  c.take(j.chstats, K * kStatStride);
-  c.take(j.history, (size_t)j.max_iter * kHistStride);
   c.take(j.mrg, j.rng ? (size_t)kMrgTables * kMrgEntry + (K + 1) * 6 : 0);
 }
 
@@ -460,6 +460,93 @@ mcv_status job_create(const mcv_problem* p, int gmax, int64_t n_points, int n_cu
   *out = j;
   *block = dev;
   return MCV_OK;
+}
+
+void HostRead::reserve(size_t bytes) {
+  if (hipHostMalloc(&pin, bytes, hipHostMallocDefault) == hipSuccess) {
+    cap = bytes;
+  } else {
+    (void)hipGetLastError();
+    pin = nullptr;
+  }
+}
+
+void HostRead::release() {
+  if (pin) hipHostFree(pin);
+  pin = nullptr;
+  cap = 0;
+}
+
+mcv_status HostRead::read(const HostSeg* seg, int n, hipStream_t s) {
+  constexpr size_t kGap = 4096;  // a copy's start costs as much as some 100 KB of it
+  std::vector<HostSeg> run;      // neighbours joined: dst = offset in the buffer
+  size_t sum = 0;
+  for (int i = 0; i < n; ++i) {
+    if (!seg[i].dst || seg[i].bytes == 0) continue;
+    const char* p = static_cast<const char*>(seg[i].src);
+    if (!run.empty()) {
+      HostSeg& r = run.back();
+      const char* e = static_cast<const char*>(r.src) + r.bytes;
+      if (p >= e && (size_t)(p - e) <= kGap) {
+        sum += (size_t)(p - e) + seg[i].bytes;
+        r.bytes = (size_t)(p - static_cast<const char*>(r.src)) + seg[i].bytes;
+        continue;
+      }
+    }
+    run.push_back(HostSeg{nullptr, p, seg[i].bytes});
+    sum += seg[i].bytes;
+  }
+  std::unique_lock<std::mutex> lk(mu, std::defer_lock);
+  char small[kReadSmall];
+  char* buf = nullptr;
+  if (sum <= cap) {
+    lk.lock();
+    buf = static_cast<char*>(pin);
+  } else if (sum <= kReadSmall) {
+    buf = small;
+  }
+  if (!buf) {
+    for (int i = 0; i < n; ++i)
+      if (seg[i].dst && seg[i].bytes)
+        MCV_HIP(hipMemcpyAsync(seg[i].dst, seg[i].src, seg[i].bytes, hipMemcpyDeviceToHost, s));
+    MCV_HIP(hipStreamSynchronize(s));
+    return MCV_OK;
+  }
+  size_t off = 0;
+  hipError_t e = hipSuccess;
+  for (HostSeg& r : run) {
+    r.dst = buf + off;
+    off += r.bytes;
+    if (e == hipSuccess) e = hipMemcpyAsync(r.dst, r.src, r.bytes, hipMemcpyDeviceToHost, s);
+  }
+  const hipError_t e2 = hipStreamSynchronize(s);  // also after an error: buf must be idle
+  MCV_HIP(e);
+  MCV_HIP(e2);
+  for (int i = 0; i < n; ++i) {
+    if (!seg[i].dst || seg[i].bytes == 0) continue;
+    const char* p = static_cast<const char*>(seg[i].src);
+    for (const HostSeg& r : run) {
+      const char* b = static_cast<const char*>(r.src);
+      if (p >= b && p + seg[i].bytes <= b + r.bytes) {
+        memcpy(seg[i].dst, static_cast<const char*>(r.dst) + (p - b), seg[i].bytes);
+        break;
+      }
+    }
+  }
+  return MCV_OK;
+}
+
+void state_segs(const JobDev& j, double* edges, double* alpha, int64_t* alloc, HostSeg (&seg)[4]) {
+  seg[0] = HostSeg{edges, j.edges, (size_t)j.K * j.d * (j.n + 1) * sizeof(double)};
+  seg[1] = HostSeg{alpha, j.alpha, j.K * sizeof(double)};
+  seg[2] = HostSeg{alloc, j.nc, j.K * sizeof(int64_t)};
+  seg[3] = HostSeg{alloc ? alloc + j.K : nullptr, j.start + j.K, sizeof(int64_t)};
+}
+
+size_t state_read_bytes(const JobDev& j) {
+  const size_t st = (const char*)(j.start + j.K + 1) - (const char*)j.edges;
+  const size_t ps = (const char*)(j.chstats + (size_t)j.K * kStatStride) - (const char*)j.hist;
+  return st > ps ? st : ps;
 }
 
 void combine_history(const double* hist, int n, int first, mcv_summary* out) {

@@ -8,6 +8,7 @@
 #include <vector>
 
 #include "mcv.h"
+#include "mcv_host.h"
 #include "mcv_internal.h"
 
 namespace mcv {
@@ -49,6 +50,7 @@ struct Engine {
     bool graphed = false;
   };
   std::vector<Ev> ev;
+  HostRead rd;  // reads of a job's state and history (a batch's)
 
   ~Engine();
   mcv_status add_job(const mcv_problem* p, int64_t n_points, int* index);

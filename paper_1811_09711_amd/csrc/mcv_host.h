@@ -5,6 +5,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <mutex>
 #include <string>
 
 #include "mcv.h"
@@ -57,6 +58,37 @@ size_t job_block_bytes(const mcv_problem* p, int gmax);
 size_t partial_bytes(const JobDev& j, int G);
 // Points the job's partial buffers into `base` (partial_bytes(j, G) bytes).
 void carve_partials(JobDev& j, int G, char* base);
+
+// Copies of device arrays of one job's block to the host, ordered on a stream
+// and waited for.  Arrays that lie close together (carved one after another)
+// are fetched by one copy.  A copy into pageable memory costs 11 to 20 us each
+// and more above 64 KB (108 us for 313 KB), one into pinned memory 14 us at
+// that size; so what an object reads repeatedly goes through a pinned buffer
+// that it keeps, made with it if one reading takes more than kReadSmall bytes
+// (making one costs 55 to 70 us, which a small job would not earn back), and
+// smaller readings through the stack.
+constexpr size_t kReadSmall = 16 << 10;
+
+struct HostSeg {
+  void* dst;        // null: not wanted
+  const void* src;
+  size_t bytes;
+};
+
+struct HostRead {
+  void* pin = nullptr;
+  size_t cap = 0;
+  std::mutex mu;  // readers of one object on several threads share the buffer
+
+  void reserve(size_t bytes);  // without memory: readings go straight to their places
+  void release();
+  mcv_status read(const HostSeg* seg, int n, hipStream_t s);
+};
+
+// Bytes of the largest single reading of a job's arrays.
+size_t state_read_bytes(const JobDev& j);
+// The segments of edges, alpha and the allocation (N_c and their total).
+void state_segs(const JobDev& j, double* edges, double* alpha, int64_t* alloc, HostSeg (&seg)[4]);
 
 // Inverse-variance weighted mean of history rows [first, n) (kHistStride
 // doubles each), its error and chi^2/ndf; iterations with zero error are
