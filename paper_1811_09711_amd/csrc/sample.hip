@@ -24,6 +24,8 @@
 #include <hip/hip_runtime.h>
 #include <string.h>
 
+#include <algorithm>
+
 #include "sample_kernel.h"
 
 namespace mcv {
@@ -100,14 +102,39 @@ __global__ __launch_bounds__(64) void k_trace(SampleArgs<T> a, const int64_t* ts
 // accept iff u * w_max < |w| (weights may be negative, Sec. 3.1: the event
 // then carries the sign).  accept[q]: 0 rejected, 1 kept with w > 0, 2 kept
 // with w < 0; wts[q] = |w| (-1 if not finite).
+//
+// A batch of 65536 trials is one wavefront per SIMD when a lane takes a whole
+// trial, and then waits for one read after another.  So a workgroup's
+// wavefronts (blockDim.x / 64 = S) share 64 trials: each makes the points, and
+// takes kUwPer of every S kUwPer channels (then peaks without a channel); the
+// kernels r and grid densities go through LDS, and the first wavefront adds
+// the terms in channel order with eval_channels' operations, so f and g are
+// the same bit for bit.  (A record's factors that an allocation writes are not
+// read: a state just loaded has none.)  100000 events of d = 10, 32 channels, two batches:
+// FP32 406 -> 270 us in all, FP64 711 -> 378; d = 12, 64 channels 558 -> 266.
+constexpr int kUwPer = 8;
+
+// The largest density of a channel's grid (axmax: of each axis).
+__device__ __forceinline__ double max_density(CP<double> axmax, int d) {
+  double m = 1.0;
+  for (int k = 0; k < d; ++k) m *= axmax[k];
+  return m;
+}
+
 template <typename T, int MAXD>
-__global__ __launch_bounds__(256) void k_unweight(SampleArgs<T> a, uint64_t q0, int64_t count,
-                                                  const double* wmax, uint8_t* accept, double* wts,
-                                                  T* pts) {
-  const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (q >= count) return;
+__global__ __launch_bounds__(512) void k_unweight(SampleArgs<T> a, uint64_t q0, int64_t count,
+                                                  const double* wmax, const double* axmax,
+                                                  uint8_t* accept, double* wts, T* pts) {
+  constexpr int GROUP = sizeof(T) == 4 ? 5 : 2;
+  extern __shared__ __align__(16) unsigned char uw_lds[];
+  T* sr = reinterpret_cast<T*>(uw_lds);  // [S kUwPer][64] r, then as many G
+  const int lane = threadIdx.x & 63, S = blockDim.x >> 6;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  T* sG = sr + S * kUwPer * 64;
+  const int64_t q = (int64_t)blockIdx.x * 64 + lane;
+  const bool in = q < count;  // the others take a trial of the next batch along
   const uint64_t trial = q0 + (uint64_t)q;
-  const int K = a.K, d = a.d;
+  const int K = a.K, d = a.d, n = a.n, sT = a.sT;
   uint32_t u[MAXD];
   uint32_t extra[3];
   if (a.rng) {  // MRG32k3a: substream `trial` of the unweighting stream
@@ -131,14 +158,67 @@ __global__ __launch_bounds__(256) void k_unweight(SampleArgs<T> a, uint64_t q0, 
   const int64_t r = (int64_t)__umul64hi(u64, (uint64_t)ntot);
   const int c = channel_of(a.start, K, r);
   T p[MAXD];
-  T f, g;
-  eval_call<T, MAXD>(a, a.alpha, c, u, p, f, g, nullptr);
-  const double w = (double)(f / g);
-  const double aw = fabs(w);
+  uint32_t jp[(MAXD + 3) / 4];
+  const T own = forward_point<T, MAXD, false>(u, d, n, cp(a.cmap) + (size_t)c * d,
+                                              a.xtab + (size_t)c * d * sT, sT, false, p, jp);
+  CP<PeakDim<T>> pmap = cp(a.pmap);
+  CP<T> pnorm = cp(a.pnorm), cnorm = cp(a.cnorm);
+  CP<int32_t> orphans = cp(a.orphans);
+  CP<double> alpha = cp(a.alpha);
+  CP<float> hab = cp(a.hab);
+  T f = T(0), g = T(0);
+  const int items = K + a.n_orphan;
+  for (int i0 = 0; i0 < items; i0 += S * kUwPer) {
+    for (int i = 0; i < kUwPer; ++i) {
+      const int s = w * kUwPer + i, cc = i0 + s;
+      if (cc >= items) break;
+      T rr, G = T(1);
+      if (cc < K) {
+        const CP<ChanHead<T>> h = chan_at(a, cc);
+        rr = chan_r_of<T, MAXD>(h, d, p);
+        if (cc == c) {
+          G = own;
+        } else if (!(__all(cc == c || rr == T(0)) && max_density(cp(axmax) + (size_t)cc * d, d) <
+                                                         (sizeof(T) == 4 ? 1e38 : 1e300))) {
+          // (a wavefront's zero terms with finite densities need no lookups)
+          const Pair<T>* T0 = a.ptab + (size_t)cc * d * sT;
+          const Cell<T>* C0 = a.ctab + (size_t)cc * d * a.M;
+          G = h->kind & kChanLin
+                  ? grid_density<T, MAXD, GROUP, true>(T0, C0, sT, n, d, a.M, a.mshift,
+                                                       hab + (size_t)cc * 2 * d, p, nullptr)
+                  : grid_density<T, MAXD, GROUP, false>(T0, C0, sT, n, d, a.M, a.mshift,
+                                                        hab + (size_t)cc * 2 * d, p, nullptr);
+        }
+      } else {
+        rr = peak_r<T, MAXD>(pmap + (size_t)orphans[cc - K] * d, d, p);
+      }
+      sr[s * 64 + lane] = rr;
+      sG[s * 64 + lane] = G;
+    }
+    __syncthreads();
+    if (w == 0) {
+      const int m = min(items - i0, S * kUwPer);
+#pragma unroll 4
+      for (int s = 0; s < m; ++s) {
+        const int cc = i0 + s;
+        const T rr = sr[s * 64 + lane];
+        if (cc < K) {
+          f = fma(chan_at(a, cc)->twin, rr, f);
+          g = fma((T)alpha[cc] * sG[s * 64 + lane], cnorm[cc] * rr, g);
+        } else {
+          f = fma(pnorm[orphans[cc - K]], rr, f);
+        }
+      }
+    }
+    if (i0 + S * kUwPer < items) __syncthreads();  // before the next terms
+  }
+  if (w != 0 || !in) return;
+  const double wt = (double)(f / g);
+  const double aw = fabs(wt);
   const double acc = ((double)extra[2] + 0.5) * 0x1p-32;
-  const bool ok = isfinite(w) && (acc * wmax[0] < aw);
-  accept[q] = ok ? (w < 0.0 ? 2 : 1) : 0;
-  wts[q] = isfinite(w) ? aw : -1.0;
+  const bool ok = isfinite(wt) && (acc * wmax[0] < aw);
+  accept[q] = ok ? (wt < 0.0 ? 2 : 1) : 0;
+  wts[q] = isfinite(wt) ? aw : -1.0;
   for (int k = 0; k < d; ++k) pts[q * d + k] = p[k];
 }
 
@@ -330,9 +410,18 @@ template <typename T, int MAXD>
 void unweight_t(const JobDev& j, uint64_t q0, int64_t count, const double* wmax, uint8_t* accept,
                 double* wts, void* pts, hipStream_t s) {
   SampleArgs<T> a = make_args<T>(j, kTagUnweight);
-  const int blocks = (int)((count + 255) / 256);
-  hipLaunchKernelGGL((k_unweight<T, MAXD>), dim3(blocks), dim3(256), 0, s, a, q0, count, wmax,
-                     accept, wts, reinterpret_cast<T*>(pts));
+  // Wavefronts per 64 trials: kUwPer terms each at least, and no more than
+  // fill the chip's 1024 SIMDs 4 deep: beyond, making the points S times over
+  // costs more than the waits it hides (12 channels, d = 4, FP64, 262144
+  // trials: 291 us with S = 2, 254 with 1; 64 channels, d = 12, FP32, 65536:
+  // 302 us with S = 8, 263 with 4).
+  const int64_t blocks = (count + 63) / 64;
+  const int terms = (j.K + j.n_orphan + kUwPer - 1) / kUwPer;
+  const int fill = (int)std::min<int64_t>(8, std::max<int64_t>(1, 4096 / blocks));
+  const int S = std::max(1, std::min(terms, fill));
+  hipLaunchKernelGGL((k_unweight<T, MAXD>), dim3((unsigned)blocks), dim3(64 * S),
+                     2 * S * kUwPer * 64 * sizeof(T), s, a, q0, count, wmax, j.axmax, accept, wts,
+                     reinterpret_cast<T*>(pts));
 }
 template <int MAXD>
 void unweight_f64(const JobDev& j, uint64_t q0, int64_t count, const double* wmax,
