@@ -83,15 +83,19 @@ Engine::~Engine() {
 
 // Units per job, partial buffers, device job table, unit prefix, sample
 // arguments and the persistent grid for the jobs listed in `listed`.  The set
-// holds them ordered by dimension (stable), so that the units of one
-// dimension are contiguous and the batched kernel's workgroups on one XCD
-// mostly run the body compiled for one d.
+// holds them ordered from the costliest call to the cheapest (by dimension,
+// then channels; stable): the last units of a pass are short ones, and those of
+// one dimension are contiguous, so that the batched kernel's workgroups on one
+// XCD mostly run the body compiled for one d.
 mcv_status Engine::build_set(const std::vector<int>& listed) {
   MCV_HIP(hipStreamSynchronize(stream));  // earlier passes may still read the table
   drop_graphs();
   std::vector<int> members = listed;
   std::stable_sort(members.begin(), members.end(),
-                   [this](int x, int y) { return jobs[x].j.d < jobs[y].j.d; });
+                   [this](int x, int y) {
+                     const JobDev &a = jobs[x].j, &b = jobs[y].j;
+                     return a.d != b.d ? a.d > b.d : a.K > b.K;
+                   });
   const int n = (int)members.size();
   set_members = members;
   set_jobs.clear();

@@ -809,13 +809,19 @@ __device__ __forceinline__ S load_uniform(const S* p) {
 // that broadcasts the unit index) come from args[jb].  A unit's result does
 // not depend on which workgroup runs it.
 //
-// The units are split into kQueues contiguous ranges, one queue each
-// (counter[q] counts the units taken from range q).  Workgroups are
-// dispatched to the chip's 8 XCDs in turn (workgroup w on XCD w mod 8), so
-// workgroup w drains queue w mod 8 first: every XCD works on a contiguous
-// stretch of jobs and its own L2 holds only their hint-cell tables.  A
-// workgroup whose queue is empty takes units from the next queues in turn,
-// and leaves once every queue is empty.  The counters are zeroed by the
+// The units, whose jobs are ordered from the costliest call to the cheapest,
+// are dealt to kQueues queues in chunks (chunk i to queue i mod kQueues;
+// counter[q] counts the units taken from queue q).  Workgroups are dispatched
+// to the chip's 8 XCDs in turn (workgroup w on XCD w mod 8), so workgroup w
+// drains queue w mod 8 first: an XCD's workgroups run a contiguous stretch of
+// jobs at a time and its own L2 holds only their hint-cell tables, while every
+// queue ends with cheap units.  A chunk is what an XCD runs at once, or less
+// where that would leave a queue fewer than 4 chunks.  (One contiguous range
+// per queue, cheapest jobs first, left the XCDs with unequal work and the
+// costliest units to the end: 48 jobs FP64 14.5 ms in place of 11.8, 128 jobs
+// FP64 34.8 and 28.0, serving 16 jobs 9.25 and 8.6, 256 jobs FP32 148.5 and
+// 146.5.)  A workgroup whose queue is empty takes units from the next queues
+// in turn, and leaves once every queue is empty.  The counters are zeroed by the
 // allocation kernel before each pass.  LB: the launch bound (largest
 // workgroup size); 512 leaves the compiler more registers per lane, 256 caps
 // them for at least 6 (FP32; 69.1 ms on the 256-job batch, against 69.9 at 7
@@ -827,7 +833,7 @@ constexpr int kQueues = 8;
 // exactly (no per-axis guards; the grouped hint-cell reads cover only the
 // job's axes, where a 12-axis body would read 5, 10 or 15 cells for any d),
 // a larger d through the generic body of the bucket MAXD.  d is uniform over
-// the workgroup, and the set orders its jobs by d, so the workgroups of one
+// the workgroup, and the set orders its jobs by d first, so the workgroups of one
 // XCD mostly run one body at a time.
 template <typename T, int MAXD, bool TB>
 __device__ __forceinline__ void queue_unit(const SampleArgs<T>& a, int u, int G, uint32_t tag,
@@ -867,17 +873,17 @@ __global__ __launch_bounds__(LB, LB == 256 ? (sizeof(T) == 4 ? 6 : 4) : 1) void 
   int* bcast = reinterpret_cast<int*>(smem);
   CP<int> pf = cp(prefix);
   const int home = (int)(blockIdx.x % kQueues);
+  const int chunk = max(1, min((int)gridDim.x / kQueues, n_units / (4 * kQueues)));
   int tried = 0;  // queues found empty (thread 0's view; the unit is broadcast)
   for (;;) {
     if (threadIdx.x == 0) {
       int unit = -1;
       while (tried < kQueues) {
         const int q = (home + tried) % kQueues;
-        const int lo = (int)((int64_t)n_units * q / kQueues);
-        const int hi = (int)((int64_t)n_units * (q + 1) / kQueues);
-        const int k = lo < hi ? atomicAdd(counter + q, 1) : 0;
-        if (lo + k < hi) {
-          unit = lo + k;
+        const int k = atomicAdd(counter + q, 1);
+        const int64_t u = ((int64_t)(k / chunk) * kQueues + q) * chunk + k % chunk;
+        if (u < n_units) {
+          unit = (int)u;
           break;
         }
         ++tried;
