@@ -323,6 +323,14 @@ __device__ void snap_axis32(int n, double* e) {
 // below a cell and in it are two binary searches over the edges' cells.
 constexpr int kAxisBlock = 256;
 
+// Threads per axis: 256 while every axis' workgroup is resident at once (the
+// hint cells are the longest loop); beyond, one wavefront, since the serial
+// sums leave the others idle and eight 256-thread workgroups fill a CU (48
+// jobs of up to 64 channels and 12 axes, FP64, 50 bins: 86 -> 53 us).
+inline int axis_block(const JobSet& js) {
+  return (int64_t)js.maxKd * js.n <= 8 * 256 ? kAxisBlock : 64;
+}
+
 template <typename T>
 __device__ void axis_tables(const JobDev& j, int ax, const double* e, Pair<T>* P, uint16_t* cells,
                             double* wmax) {
@@ -333,7 +341,7 @@ __device__ void axis_tables(const JobDev& j, int ax, const double* e, Pair<T>* P
   const bool log_map = !j.ctype[ax / j.d].lin;  // the map the lookups of this channel use
   const float ha = j.hab[2 * ax], hb = j.hab[2 * ax + 1];
   double mx = 0.0;
-  for (int i = tid; i < sT; i += kAxisBlock) {
+  for (int i = tid; i < sT; i += blockDim.x) {
     const T dens = (i < n) ? (T)(1.0 / ((double)n * (e[i + 1] - e[i]))) : T(0);
     X[i] = Pair<T>{i <= n ? (T)e[i] : T(1), dens};
     T pe;
@@ -352,11 +360,11 @@ __device__ void axis_tables(const JobDev& j, int ax, const double* e, Pair<T>* P
   if ((tid & 63) == 0) wmax[tid >> 6] = mx;
   __syncthreads();
   if (tid == 0) {
-    for (int w = 1; w < kAxisBlock / 64; ++w) mx = fmax(mx, wmax[w]);
+    for (int w = 1; w < (int)blockDim.x / 64; ++w) mx = fmax(mx, wmax[w]);
     j.axmax[ax] = mx;
   }
   Cell<T>* C = (Cell<T>*)j.ctab + (size_t)ax * M;
-  for (int c = tid; c < M; c += kAxisBlock) {
+  for (int c = tid; c < M; c += blockDim.x) {
     int lo = 1, hi = n;
     while (lo < hi) {  // first edge whose cell is >= c (n if none)
       const int mid = (lo + hi) >> 1;
@@ -415,7 +423,7 @@ __global__ __launch_bounds__(kAxisBlock) void k_tables(const JobDev* jobs) {
   const JobDev& j = jobs[blockIdx.y];
   const int ax = blockIdx.x;
   if (ax >= j.K * j.d) return;  // uniform over the workgroup
-  for (int i = threadIdx.x; i <= j.n; i += kAxisBlock) sh.es[i] = j.edges[(size_t)ax * (j.n + 1) + i];
+  for (int i = threadIdx.x; i <= j.n; i += blockDim.x) sh.es[i] = j.edges[(size_t)ax * (j.n + 1) + i];
   __syncthreads();
   axis_tables<T>(j, ax, sh.es, reinterpret_cast<Pair<T>*>(sh.P), sh.cells, sh.wmax);
 }
@@ -905,8 +913,8 @@ __device__ void refine_axis(const JobDev& j, int ax, AxisShared& sh) {
   const int n = j.n, tid = threadIdx.x;
   double* e = j.edges + (size_t)ax * (n + 1);
   const double* h = (j.n_eq > 0 ? j.hist_eq : j.hist) + (size_t)ax * n;
-  for (int i = tid; i < n; i += kAxisBlock) om[i] = sqrt(h[i]);
-  for (int i = tid; i <= n; i += kAxisBlock) es[i] = e[i];  // the walk reads LDS
+  for (int i = tid; i < n; i += blockDim.x) om[i] = sqrt(h[i]);
+  for (int i = tid; i <= n; i += blockDim.x) es[i] = e[i];  // the walk reads LDS
   __syncthreads();
   if (tid == 0) {  // the ordered sum
     double sum = 0.0;
@@ -919,7 +927,7 @@ __device__ void refine_axis(const JobDev& j, int ax, AxisShared& sh) {
   if (!(sum > 0.0) || !isfinite(sum)) return;  // nothing to adapt to (uniform)
   const double a = j.grid_power;
   // the per-bin weights of eq. 30 are independent: one bin per lane
-  for (int i = tid; i < n; i += kAxisBlock) {
+  for (int i = tid; i < n; i += blockDim.x) {
     const double r = om[i] / sum;
     double v;
     if (r == 0.0) v = 0.0;
@@ -948,7 +956,7 @@ __device__ void refine_axis(const JobDev& j, int ax, AxisShared& sh) {
   }
   __syncthreads();
   const double M = pre[n];
-  for (int i = tid + 1; i < n; i += kAxisBlock) {
+  for (int i = tid + 1; i < n; i += blockDim.x) {
     const double target = ((double)i * M) / (double)n;
     int lo = 0, hi = n - 1;  // first b in [0, n - 1) with pre[b + 1] >= target, else n - 1
     while (lo < hi) {
@@ -965,7 +973,7 @@ __device__ void refine_axis(const JobDev& j, int ax, AxisShared& sh) {
   // nothing when no pair violates them: every lane checks its pairs, and
   // lane 0 runs them only if some pair does.
   bool bad = false;
-  for (int i = tid + 1; i < n; i += kAxisBlock)
+  for (int i = tid + 1; i < n; i += blockDim.x)
     bad |= !(out[i] > out[i - 1]) || !(out[i] < out[i + 1]);
   if (__syncthreads_or(bad)) {
     if (tid == 0) {
@@ -978,18 +986,18 @@ __device__ void refine_axis(const JobDev& j, int ax, AxisShared& sh) {
   }
   if (sizeof(T) == 4) {
     bool bad32 = false;
-    for (int i = tid + 1; i < n; i += kAxisBlock) {
+    for (int i = tid + 1; i < n; i += blockDim.x) {
       const float f = (float)out[i];
       bad32 |= !(f > (float)out[i - 1]) || !(f < (float)out[i + 1]);
     }
     if (__syncthreads_or(bad32)) {
       if (tid == 0) snap_axis32(n, out);
     } else {
-      for (int i = tid + 1; i < n; i += kAxisBlock) out[i] = (double)(float)out[i];
+      for (int i = tid + 1; i < n; i += blockDim.x) out[i] = (double)(float)out[i];
     }
     __syncthreads();
   }
-  for (int i = tid; i <= n; i += kAxisBlock) e[i] = out[i];
+  for (int i = tid; i <= n; i += blockDim.x) e[i] = out[i];
   axis_tables<T>(j, ax, out, reinterpret_cast<Pair<T>*>(sh.P), sh.cells, sh.wmax);
 }
 
@@ -1059,9 +1067,9 @@ void launch_setup(const JobDev& j, hipStream_t s) {
 void launch_tables(const JobSet& js, hipStream_t s) {
   if (js.n < 1) return;
   if (js.prec == 1)
-    hipLaunchKernelGGL(k_tables<float>, dim3(js.maxKd, js.n), dim3(kAxisBlock), 0, s, js.dev);
+    hipLaunchKernelGGL(k_tables<float>, dim3(js.maxKd, js.n), dim3(axis_block(js)), 0, s, js.dev);
   else
-    hipLaunchKernelGGL(k_tables<double>, dim3(js.maxKd, js.n), dim3(kAxisBlock), 0, s, js.dev);
+    hipLaunchKernelGGL(k_tables<double>, dim3(js.maxKd, js.n), dim3(axis_block(js)), 0, s, js.dev);
 }
 
 void launch_allocate(const JobSet& js, int64_t n_override, bool to_trace, hipStream_t s) {
@@ -1090,10 +1098,10 @@ void launch_refine(const JobSet& js, bool grid, bool alpha, hipStream_t s) {
     hipLaunchKernelGGL(k_equivalences, dim3(js.maxKd, js.n), dim3(64), 0, s, js.dev);
   const dim3 g((grid ? js.maxKd : 0) + (alpha ? 1 : 0), js.n);
   if (js.prec == 1)
-    hipLaunchKernelGGL(k_refine<float>, g, dim3(kAxisBlock), 0, s, js.dev, grid ? 1 : 0,
+    hipLaunchKernelGGL(k_refine<float>, g, dim3(axis_block(js)), 0, s, js.dev, grid ? 1 : 0,
                        alpha ? 1 : 0);
   else
-    hipLaunchKernelGGL(k_refine<double>, g, dim3(kAxisBlock), 0, s, js.dev, grid ? 1 : 0,
+    hipLaunchKernelGGL(k_refine<double>, g, dim3(axis_block(js)), 0, s, js.dev, grid ? 1 : 0,
                        alpha ? 1 : 0);
 }
 
