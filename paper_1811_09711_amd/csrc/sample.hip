@@ -104,8 +104,8 @@ __global__ __launch_bounds__(64) void k_trace(SampleArgs<T> a, const int64_t* ts
 // with w < 0; wts[q] = |w| (-1 if not finite).
 //
 // A batch of 65536 trials is one wavefront per SIMD when a lane takes a whole
-// trial, and then waits for one read after another.  So a workgroup's
-// wavefronts (blockDim.x / 64 = S) share 64 trials: each makes the points, and
+// trial, and then waits for one read after another.  So groups of S
+// wavefronts of a workgroup share 64 trials: each makes the points, and
 // takes kUwPer of every S kUwPer channels (then peaks without a channel); the
 // kernels r and grid densities go through LDS, and the first wavefront adds
 // the terms in channel order with eval_channels' operations, so f and g are
@@ -123,15 +123,17 @@ __device__ __forceinline__ double max_density(CP<double> axmax, int d) {
 
 template <typename T, int MAXD>
 __global__ __launch_bounds__(512) void k_unweight(SampleArgs<T> a, uint64_t q0, int64_t count,
-                                                  const double* wmax, const double* axmax,
+                                                  const double* wmax, const double* axmax, int S,
                                                   uint8_t* accept, double* wts, T* pts) {
   constexpr int GROUP = sizeof(T) == 4 ? 5 : 2;
   extern __shared__ __align__(16) unsigned char uw_lds[];
-  T* sr = reinterpret_cast<T*>(uw_lds);  // [S kUwPer][64] r, then as many G
-  const int lane = threadIdx.x & 63, S = blockDim.x >> 6;
-  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int group = wave / S, w = wave % S;  // S wavefronts each
+  // the group's r [S kUwPer][64], then as many G (S = 1 needs none)
+  T* sr = reinterpret_cast<T*>(uw_lds) + (size_t)group * 2 * S * kUwPer * 64;
   T* sG = sr + S * kUwPer * 64;
-  const int64_t q = (int64_t)blockIdx.x * 64 + lane;
+  const int64_t q = ((int64_t)blockIdx.x * (blockDim.x / (64 * S)) + group) * 64 + lane;
   const bool in = q < count;  // the others take a trial of the next batch along
   const uint64_t trial = q0 + (uint64_t)q;
   const int K = a.K, d = a.d, n = a.n, sT = a.sT;
@@ -192,9 +194,19 @@ __global__ __launch_bounds__(512) void k_unweight(SampleArgs<T> a, uint64_t q0, 
       } else {
         rr = peak_r<T, MAXD>(pmap + (size_t)orphans[cc - K] * d, d, p);
       }
+      if (S == 1) {  // uniform
+        if (cc < K) {
+          f = fma(chan_at(a, cc)->twin, rr, f);
+          g = fma((T)alpha[cc] * G, cnorm[cc] * rr, g);
+        } else {
+          f = fma(pnorm[orphans[cc - K]], rr, f);
+        }
+        continue;
+      }
       sr[s * 64 + lane] = rr;
       sG[s * 64 + lane] = G;
     }
+    if (S == 1) continue;
     __syncthreads();
     if (w == 0) {
       const int m = min(items - i0, S * kUwPer);
@@ -419,8 +431,10 @@ void unweight_t(const JobDev& j, uint64_t q0, int64_t count, const double* wmax,
   const int terms = (j.K + j.n_orphan + kUwPer - 1) / kUwPer;
   const int fill = (int)std::min<int64_t>(8, std::max<int64_t>(1, 4096 / blocks));
   const int S = std::max(1, std::min(terms, fill));
-  hipLaunchKernelGGL((k_unweight<T, MAXD>), dim3((unsigned)blocks), dim3(64 * S),
-                     2 * S * kUwPer * 64 * sizeof(T), s, a, q0, count, wmax, j.axmax, accept, wts,
+  const int groups = S < 4 ? 4 / S : 1;  // 192- to 512-thread workgroups
+  const size_t lds = S > 1 ? (size_t)groups * 2 * S * kUwPer * 64 * sizeof(T) : 0;
+  hipLaunchKernelGGL((k_unweight<T, MAXD>), dim3((unsigned)((blocks + groups - 1) / groups)),
+                     dim3(64 * S * groups), lds, s, a, q0, count, wmax, j.axmax, S, accept, wts,
                      reinterpret_cast<T*>(pts));
 }
 template <int MAXD>
