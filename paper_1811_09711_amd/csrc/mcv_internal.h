@@ -227,18 +227,18 @@ Split single_trace(const JobDev& j, int64_t n_points, uint32_t tag, int64_t firs
 // largest dimension is maxd.
 #define MCV_QUEUE_NAME(P, LB, TB) MCV_QUEUE_NAME_(P, LB, TB)
 #define MCV_QUEUE_NAME_(P, LB, TB) queue_kernel_##P##_##LB##_##TB
-const void* MCV_QUEUE_NAME(1, 256, 1)(int maxd);
-const void* MCV_QUEUE_NAME(1, 256, 0)(int maxd);
-const void* MCV_QUEUE_NAME(1, 512, 1)(int maxd);
-const void* MCV_QUEUE_NAME(1, 512, 0)(int maxd);
-const void* MCV_QUEUE_NAME(1, 1024, 1)(int maxd);
-const void* MCV_QUEUE_NAME(1, 1024, 0)(int maxd);
-const void* MCV_QUEUE_NAME(0, 256, 1)(int maxd);
-const void* MCV_QUEUE_NAME(0, 256, 0)(int maxd);
-const void* MCV_QUEUE_NAME(0, 512, 1)(int maxd);
-const void* MCV_QUEUE_NAME(0, 512, 0)(int maxd);
-const void* MCV_QUEUE_NAME(0, 1024, 1)(int maxd);
-const void* MCV_QUEUE_NAME(0, 1024, 0)(int maxd);
+const void* MCV_QUEUE_NAME(1, 256, 1)(int maxd, bool pair);
+const void* MCV_QUEUE_NAME(1, 256, 0)(int maxd, bool pair);
+const void* MCV_QUEUE_NAME(1, 512, 1)(int maxd, bool pair);
+const void* MCV_QUEUE_NAME(1, 512, 0)(int maxd, bool pair);
+const void* MCV_QUEUE_NAME(1, 1024, 1)(int maxd, bool pair);
+const void* MCV_QUEUE_NAME(1, 1024, 0)(int maxd, bool pair);
+const void* MCV_QUEUE_NAME(0, 256, 1)(int maxd, bool pair);
+const void* MCV_QUEUE_NAME(0, 256, 0)(int maxd, bool pair);
+const void* MCV_QUEUE_NAME(0, 512, 1)(int maxd, bool pair);
+const void* MCV_QUEUE_NAME(0, 512, 0)(int maxd, bool pair);
+const void* MCV_QUEUE_NAME(0, 1024, 1)(int maxd, bool pair);
+const void* MCV_QUEUE_NAME(0, 1024, 0)(int maxd, bool pair);
 // Largest co-resident workgroups per CU of the batched kernel for a set.
 int sample_queue_occupancy(const JobSet& js);
 // One persistent launch over the set's work-unit queue.

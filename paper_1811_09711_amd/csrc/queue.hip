@@ -19,9 +19,12 @@ constexpr bool kTB = MCV_QUEUE_TB != 0;
 
 // Two buckets by the set's largest dimension: up to 12 (a body per d), and
 // up to 32 (the same, plus one generic body for d > 12).
-const void* MCV_QUEUE_NAME(MCV_QUEUE_FP32, MCV_QUEUE_LB, MCV_QUEUE_TB)(int maxd) {
-  if (maxd <= 12) return (const void*)k_sample_queue<QT, 12, MCV_QUEUE_LB, kTB>;
-  return (const void*)k_sample_queue<QT, 32, MCV_QUEUE_LB, kTB>;
+const void* MCV_QUEUE_NAME(MCV_QUEUE_FP32, MCV_QUEUE_LB, MCV_QUEUE_TB)(int maxd, bool pair) {
+#if !MCV_QUEUE_FP32
+  if (pair && maxd <= 12) return (const void*)k_sample_queue<QT, 12, MCV_QUEUE_LB, kTB, true>;
+#endif
+  if (maxd <= 12) return (const void*)k_sample_queue<QT, 12, MCV_QUEUE_LB, kTB, false>;
+  return (const void*)k_sample_queue<QT, 32, MCV_QUEUE_LB, kTB, false>;
 }
 
 }  // namespace mcv

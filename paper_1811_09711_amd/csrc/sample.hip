@@ -376,22 +376,28 @@ __global__ __launch_bounds__(256) void k_compact_final(int ntiles, const int64_t
   } while (0)
 
 // The batched kernel of a set: precision, launch bound (256, 512 or 1024,
-// the smallest that holds the set's), term-bound option, largest dimension.
+// the smallest that holds the set's), term-bound option, largest dimension,
+// pair path.
 const void* queue_kernel(const JobSet& js) {
   const int lb = js.bound > 512 ? 1024 : js.bound > 256 ? 512 : 256;
   const int m = js.maxd;
+  // Pair channels' own path (FP64, pair_density) where every unit is resident at
+  // once, at 16 waves per CU: such a pass waits for one read after another (48
+  // jobs, 973 units: 14.8 -> 11.5 ms with it); beyond, its registers cost more
+  // than they save (256 jobs: 162.6 -> 174 ms; 128 jobs: 28.1 -> 29.4).
+  const bool pair = (int64_t)js.n_units * (js.block / 64) <= 16 * (int64_t)js.host[0].n_cu;
   if (js.prec == 1) {
     if (js.term_bound)
-      return lb == 1024 ? MCV_QUEUE_NAME(1, 1024, 1)(m)
-             : lb == 512 ? MCV_QUEUE_NAME(1, 512, 1)(m) : MCV_QUEUE_NAME(1, 256, 1)(m);
-    return lb == 1024 ? MCV_QUEUE_NAME(1, 1024, 0)(m)
-           : lb == 512 ? MCV_QUEUE_NAME(1, 512, 0)(m) : MCV_QUEUE_NAME(1, 256, 0)(m);
+      return lb == 1024 ? MCV_QUEUE_NAME(1, 1024, 1)(m, pair)
+             : lb == 512 ? MCV_QUEUE_NAME(1, 512, 1)(m, pair) : MCV_QUEUE_NAME(1, 256, 1)(m, pair);
+    return lb == 1024 ? MCV_QUEUE_NAME(1, 1024, 0)(m, pair)
+           : lb == 512 ? MCV_QUEUE_NAME(1, 512, 0)(m, pair) : MCV_QUEUE_NAME(1, 256, 0)(m, pair);
   }
   if (js.term_bound)
-    return lb == 1024 ? MCV_QUEUE_NAME(0, 1024, 1)(m)
-           : lb == 512 ? MCV_QUEUE_NAME(0, 512, 1)(m) : MCV_QUEUE_NAME(0, 256, 1)(m);
-  return lb == 1024 ? MCV_QUEUE_NAME(0, 1024, 0)(m)
-         : lb == 512 ? MCV_QUEUE_NAME(0, 512, 0)(m) : MCV_QUEUE_NAME(0, 256, 0)(m);
+    return lb == 1024 ? MCV_QUEUE_NAME(0, 1024, 1)(m, pair)
+           : lb == 512 ? MCV_QUEUE_NAME(0, 512, 1)(m, pair) : MCV_QUEUE_NAME(0, 256, 1)(m, pair);
+  return lb == 1024 ? MCV_QUEUE_NAME(0, 1024, 0)(m, pair)
+         : lb == 512 ? MCV_QUEUE_NAME(0, 512, 0)(m, pair) : MCV_QUEUE_NAME(0, 256, 0)(m, pair);
 }
 
 template <typename T, int MAXD>

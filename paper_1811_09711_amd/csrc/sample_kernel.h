@@ -582,11 +582,6 @@ __device__ __forceinline__ void masked_terms(const SampleArgs<T>& a, int c, int 
 // x-space table and its per-bin sums of w^2 live in LDS.
 // ---------------------------------------------------------------------------
 
-// Pair channels (ChanHead) take their own path in the FP64 batched pass, whose
-// small units wait for one read after another.
-template <typename T, int MAXD, int BLOCK>
-constexpr bool kPairPath = sizeof(T) == 8 && BLOCK == 0 && MAXD <= 16;
-
 // One work unit of a pass: unit g of the job's G units takes the calls
 // [g N/G, (g+1) N/G).  BLOCK > 0: the workgroup size as a constant, else
 // blockDim.x.  EXACT: the job's dimension is MAXD (no per-axis guards).
@@ -600,7 +595,7 @@ constexpr bool kPairPath = sizeof(T) == 8 && BLOCK == 0 && MAXD <= 16;
 // with the same unit.  staged: the channel whose own table the workgroup holds
 // in LDS (-1: none, and the sums are not yet cleared).
 template <typename T, int MAXD, int BLOCK, bool EXACT, bool TB, bool TRACE = false, int RNG = 0,
-          int MT = 0, bool LAZY = false, bool MASK = false>
+          int MT = 0, bool LAZY = false, bool MASK = false, bool PAIR = false>
 __device__ __forceinline__ void sample_unit(const SampleArgs<T>& a, int g, int G, uint32_t tag,
                                             unsigned char* smem, int& staged) {
   static_assert(RNG == 0 || (BLOCK > 0 && (BLOCK & (BLOCK - 1)) == 0),
@@ -702,7 +697,7 @@ __device__ __forceinline__ void sample_unit(const SampleArgs<T>& a, int g, int G
         if constexpr (MASK)
           masked_terms<T, MAXD, GROUP, EXACT>(a, c, d, M, mshift, queue, p, f, gg);
         else
-          other_terms<T, MAXD, GROUP, EXACT, TB, LAZY, kPairPath<T, MAXD, BLOCK>>(a, c, d, M, mshift,
+          other_terms<T, MAXD, GROUP, EXACT, TB, LAZY, PAIR>(a, c, d, M, mshift,
                                                                                  p, f, gg);
       }
       // ---- weights and sums (FP64)
@@ -832,7 +827,7 @@ __device__ __forceinline__ S load_uniform(const S* p) {
 // workgroup size); 512 leaves the compiler more registers per lane, 256 caps
 // them for at least 6 (FP32; 69.1 ms on the 256-job batch, against 69.9 at 7
 // and 73.0 at 8) or 4 (FP64) waves per SIMD.  TB: lookups
-// guarded by the channels' term bounds.
+// guarded by the channels' term bounds.  PAIR: pair channels take their own path.
 constexpr int kQueues = 8;
 
 // One unit of a batched pass, compiled for the job's dimension: d <= 12
@@ -841,14 +836,14 @@ constexpr int kQueues = 8;
 // a larger d through the generic body of the bucket MAXD.  d is uniform over
 // the workgroup, and the set orders its jobs by d first, so the workgroups of one
 // XCD mostly run one body at a time.
-template <typename T, int MAXD, bool TB>
+template <typename T, int MAXD, bool TB, bool PAIR>
 __device__ __forceinline__ void queue_unit(const SampleArgs<T>& a, int u, int G, uint32_t tag,
                                            unsigned char* smem) {
   int staged = -1;  // the unit's job may differ from the one before
 #define MCV_EXACT_CASE(D)                                         \
   case D:                                                         \
     if constexpr (D <= MAXD) {                                    \
-      sample_unit<T, D, 0, true, TB>(a, u, G, tag, smem, staged); \
+      sample_unit<T, D, 0, true, TB, false, 0, 0, false, false, PAIR>(a, u, G, tag, smem, staged); \
       return;                                                     \
     }                                                             \
     break;
@@ -872,7 +867,7 @@ __device__ __forceinline__ void queue_unit(const SampleArgs<T>& a, int u, int G,
   if constexpr (MAXD > 12) sample_unit<T, MAXD, 0, false, TB>(a, u, G, tag, smem, staged);
 }
 
-template <typename T, int MAXD, int LB, bool TB>
+template <typename T, int MAXD, int LB, bool TB, bool PAIR>
 __global__ __launch_bounds__(LB, LB == 256 ? (sizeof(T) == 4 ? 6 : 4) : 1) void k_sample_queue(
     const SampleArgs<T>* args, const int* prefix, int n_jobs, int n_units, int* counter) {
   extern __shared__ __align__(16) unsigned char smem[];
@@ -910,7 +905,7 @@ __global__ __launch_bounds__(LB, LB == 256 ? (sizeof(T) == 4 ? 6 : 4) : 1) void 
     const int G = pf[lo + 1] - u0;
     const SampleArgs<T> a = load_uniform(args + lo);
     const uint32_t tag = (uint32_t)cp(a.iter)[0];
-    queue_unit<T, MAXD, TB>(a, u - u0, G, tag, smem);
+    queue_unit<T, MAXD, TB, PAIR>(a, u - u0, G, tag, smem);
   }
 }
 
@@ -918,13 +913,14 @@ __global__ __launch_bounds__(LB, LB == 256 ? (sizeof(T) == 4 ? 6 : 4) : 1) void 
 // capped for a number of waves per SIMD (d = 10, 32 channels, 24 Gaussian and
 // 8 Breit-Wigner: FP32 with masks 4.10, 3.93 and 4.36 ms a pass of 1e8 at 4, 5
 // and 6 waves; FP64 2.08, 1.96 and 2.4 ms a pass of 1e7 at 3, 4 and 5; FP32
-// without masks 7, where its few registers allow it).
+// without masks 7, where its few registers allow it; above 12 axes fewer: 7 spilled
+// up to 3064 registers, d = 14, 8 channels: 2.8 ms a pass of 2e6).
 template <typename T>
 struct Tune {
   static constexpr int BLOCK = 256, PPT = 1;
 };
-template <typename T, bool MASK>
-constexpr int kMinWaves = sizeof(T) == 4 ? (MASK ? 5 : 7) : 4;
+template <typename T, int MAXD, bool MASK>
+constexpr int kMinWaves = sizeof(T) == 8 || MAXD > 16 ? 4 : MASK || MAXD > 12 ? 5 : 7;
 
 // Single-job pass: as many workgroups as fit the chip at once drain the
 // pass's units in order, each taking the next one when it is done, so that
@@ -942,7 +938,7 @@ constexpr bool kLazyWalks = sizeof(T) == 4;
 
 template <typename T, int MAXD, int PPT, int BLOCK, bool EXACT, int RNG = 0, int MT = 0,
           bool MASK = false, bool TRACE = false>
-__global__ __launch_bounds__(BLOCK, (kMinWaves<T, MASK>)) void k_sample(SampleArgs<T> a) {
+__global__ __launch_bounds__(BLOCK, (kMinWaves<T, MAXD, MASK>)) void k_sample(SampleArgs<T> a) {
   static_assert(PPT == 1, "one call per thread and round");
   extern __shared__ __align__(16) unsigned char smem[];
   __shared__ int next_s;
