@@ -49,6 +49,31 @@ inline MaskForm mask_form_of(int d) {
   return mask_form(m, d == m);
 }
 
+// The features of one call at p.  An axis beyond d, where p is 0, adds nothing:
+// in the second form its q = -1/2 would enter the sum of squares, which bounds
+// the exponent from below over the d axes alone.
+template <int MAXD, bool EXACT, typename T, int N>
+__device__ __forceinline__ void mask_features(const T (&p)[MAXD], int d, float ee, float (&x)[N]) {
+  constexpr MaskForm F = mask_form(MAXD, EXACT);
+  static_assert(N == 16 * F.steps, "whole product steps");
+#pragma unroll
+  for (int k = 0; k < N; ++k) x[k] = 0.0f;
+  x[F.e] = ee;
+#pragma unroll
+  for (int k = 0; k < MAXD; ++k) {
+    const float q = EXACT || k < d ? (float)p[k] - 0.5f : 0.0f;
+    if constexpr (F.axes > 0) {
+      if (k < F.axes) {
+        x[k] = q;
+        x[F.q2 + k] = q * q;
+      }
+    } else {
+      x[k] = q;
+      x[F.q2] = fmaf(q, q, x[F.q2]);
+    }
+  }
+}
+
 // Bit j: channel 32 tile + j may change f or g on some lane of the wavefront.
 // Every lane takes part (the product ignores the execution mask).  ee: the
 // call's e = min(floor log2 f, floor log2 g), from which both sums only grow
@@ -62,27 +87,11 @@ inline MaskForm mask_form_of(int d) {
 // column l mod 32, so a lane's minimum over its registers is its channel's
 // minimum over half the calls, and the ballot's two halves join them.
 template <int MAXD, bool EXACT, typename T>
-__device__ __forceinline__ uint32_t channel_mask(const T (&p)[MAXD], float ee, const void* coef,
-                                                 const float* thr, int tile) {
-  constexpr MaskForm F = mask_form(MAXD, EXACT);
-  constexpr int MS = F.steps;
+__device__ __forceinline__ uint32_t channel_mask(const T (&p)[MAXD], int d, float ee,
+                                                 const void* coef, const float* thr, int tile) {
+  constexpr int MS = mask_form(MAXD, EXACT).steps;
   float x[16 * MS];
-#pragma unroll
-  for (int k = 0; k < 16 * MS; ++k) x[k] = 0.0f;
-  x[F.e] = ee;
-#pragma unroll
-  for (int k = 0; k < MAXD; ++k) {
-    const float q = (float)p[k] - 0.5f;
-    if constexpr (F.axes > 0) {
-      if (k < F.axes) {
-        x[k] = q;
-        x[F.q2 + k] = q * q;
-      }
-    } else {
-      x[k] = q;
-      x[F.q2] = fmaf(q, q, x[F.q2]);
-    }
-  }
+  mask_features<MAXD, EXACT>(p, d, ee, x);
   const int lane = (int)__lane_id();
   // an opaque offset, so that the loads stay in the loop over the calls
   // (cached) instead of occupying registers across it

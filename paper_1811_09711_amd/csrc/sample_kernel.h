@@ -546,7 +546,7 @@ __device__ __forceinline__ void masked_terms(const SampleArgs<T>& a, int c, int 
         base += 32;
         last = base >= K;
         if (last) break;
-        m = channel_mask<MAXD, EXACT>(p, (float)e, a.mco, a.mthr, base >> 5);
+        m = channel_mask<MAXD, EXACT>(p, d, (float)e, a.mco, a.mthr, base >> 5);
         if ((unsigned)(c - base) < 32u) m &= ~(1u << (c - base));
         continue;
       }
