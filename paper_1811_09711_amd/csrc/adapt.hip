@@ -672,10 +672,13 @@ struct Slots {
 __device__ inline Slots channel_slots(const JobDev& j, int c, const int* unit_prefix, int G1) {
   Slots r;
   r.G = unit_prefix ? unit_prefix[blockIdx.y + 1] - unit_prefix[blockIdx.y] : G1;
-  r.S = slot_chunks(r.G, j.K);
-  // the pass split the calls (or, stratified, the boxes) into G units
+  // the pass split the calls (or, stratified, the boxes) into G units, at most
+  // one for each: with more, units between two calls of a channel would be
+  // empty and leave their slots as an earlier pass wrote them
   const int64_t* st = j.strat > 0 ? j.bstart : j.start;
   const int64_t ntot = st[j.K];
+  if (r.G > ntot) r.G = (int)ntot;
+  r.S = slot_chunks(r.G, j.K);
   r.g0 = seg_of(st[c], r.G, ntot);
   r.g1 = seg_of(st[c + 1] - 1, r.G, ntot) + 1;
   return r;

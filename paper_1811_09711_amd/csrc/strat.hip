@@ -52,13 +52,15 @@ __global__ __launch_bounds__(kStratBlock, kStratMinWaves<T>) void k_sample_strat
   CP<double> alpha = cp(a.alpha);
   CP<DimMap<T>> cmap = cp(a.cmap);
   CP<T> cnorm = cp(a.cnorm);
-  const int g = blockIdx.x, G = gridDim.x;
   CP<int64_t> start = cp(a.start);
   CP<int64_t> bstart = cp(a.bstart);
   const uint32_t tag = (uint32_t)cp(a.iter)[0];
   const int64_t btot = bstart[K];
+  // no more units than boxes (the host knows the calls, not the boxes): every
+  // slot that the reduction reads is written
+  const int g = blockIdx.x, G = (int)min((int64_t)gridDim.x, btot);
+  if (g >= G) return;  // uniform
   const int64_t lo = (int64_t)g * btot / G, hi = (int64_t)(g + 1) * btot / G;
-  if (lo >= hi) return;  // uniform
   for (int t = tid; t < dn; t += kStratBlock) hist[t] = 0.0;
   int c = 0;
   while (c < K - 1 && bstart[c + 1] <= lo) ++c;
