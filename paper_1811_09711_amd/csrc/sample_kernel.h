@@ -547,6 +547,10 @@ __device__ __forceinline__ void masked_terms(const SampleArgs<T>& a, int c, int 
         last = base >= K;
         if (last) break;
         m = channel_mask<MAXD, EXACT>(p, d, (float)e, a.mco, a.mthr, base >> 5);
+        // the last tile's columns beyond the channels: their thresholds rule
+        // them out, but not where no call of the product is a number (a call
+        // without a point, as a width beyond the FP32 range gives)
+        if (K - base < 32) m &= (1u << (K - base)) - 1u;
         if ((unsigned)(c - base) < 32u) m &= ~(1u << (c - base));
         continue;
       }
