@@ -308,15 +308,17 @@ __device__ __forceinline__ CP<double> fresh(const double* p) {
   return cp(p);
 }
 
-// 2^x for x <= 1 (cut at 3e-18, about 1 ulp; below the exponent range 0).
+// 2^x for x <= 1 (cut at 3e-18, about 1 ulp; below the exponent range 0, at
+// minus infinity as well, where x - rint(x) would be no number).
 __device__ inline double m_exp2(double x) {
   const CP<double> c = fresh(kExp2Tab);
+  x = x < -4096.0 ? -4096.0 : x;  // NaN stays
   const double n = __builtin_rint(x);
   const double f = x - n;
   double P = c[0];
 #pragma unroll
   for (int i = 1; i < kExp2N; ++i) P = fma(P, f, c[i]);
-  return __builtin_amdgcn_ldexp(P, (int)fmax(n, -4096.0));
+  return __builtin_amdgcn_ldexp(P, (int)n);
 }
 // FP32: the hardware exp2 (one instruction, about 1 ulp; a result below
 // 2^-126 may come back as 0).  Every use is a density kernel
