@@ -917,14 +917,18 @@ __global__ __launch_bounds__(LB, LB == 256 ? (sizeof(T) == 4 ? 6 : 4) : 1) void 
 // capped for a number of waves per SIMD (d = 10, 32 channels, 24 Gaussian and
 // 8 Breit-Wigner: FP32 with masks 4.10, 3.93 and 4.36 ms a pass of 1e8 at 4, 5
 // and 6 waves; FP64 2.08, 1.96 and 2.4 ms a pass of 1e7 at 3, 4 and 5; FP32
-// without masks 7, where its few registers allow it; above 12 axes fewer: 7 spilled
-// up to 3064 registers, d = 14, 8 channels: 2.8 ms a pass of 2e6).
+// without masks 7, where its few registers allow it).  Above 12 axes fewer: 7
+// without masks spilled up to 3064 registers (d = 14, 8 channels: 2.8 ms a pass
+// of 2e6), and 5 with them 143 (an iteration of 2e6 calls, d = 14, 16 Gaussian
+// channels: 514 us at 5, 228 at 4, 240 at 3 and 286 without masks; d = 16: 234,
+// 222, 214 and 247).
 template <typename T>
 struct Tune {
   static constexpr int BLOCK = 256, PPT = 1;
 };
 template <typename T, int MAXD, bool MASK>
-constexpr int kMinWaves = sizeof(T) == 8 || MAXD > 16 ? 4 : MASK || MAXD > 12 ? 5 : 7;
+constexpr int kMinWaves =
+    sizeof(T) == 8 || MAXD > 16 ? 4 : MASK ? (MAXD > 12 ? 4 : 5) : MAXD > 12 ? 5 : 7;
 
 // Single-job pass: as many workgroups as fit the chip at once drain the
 // pass's units in order, each taking the next one when it is done, so that
