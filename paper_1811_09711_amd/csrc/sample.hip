@@ -112,6 +112,13 @@ __global__ __launch_bounds__(64) void k_trace(SampleArgs<T> a, const int64_t* ts
 // the same bit for bit.  (A record's factors that an allocation writes are not
 // read: a state just loaded has none.)  100000 events of d = 10, 32 channels, two batches:
 // FP32 406 -> 270 us in all, FP64 711 -> 378; d = 12, 64 channels 558 -> 266.
+//
+// SHARE: S > 1.  One wavefront for all terms is a kernel of its own, without
+// the shares' branches (batches of 262144, 48 channels, d = 12: FP32 169 -> 161
+// us, FP64 408 -> 356).  There the lookups of up to 8 axes in FP64 go one at a
+// time (20 channels, d = 7: 124 to 126 us, in pairs 131), and up to 4 axes,
+// where a lookup costs no more than the test that may leave it out, every term
+// is evaluated (6 channels, d = 3, FP64: 59 us, with the test 61).
 constexpr int kUwPer = 8;
 
 // The largest density of a channel's grid (axmax: of each axis).
@@ -121,15 +128,16 @@ __device__ __forceinline__ double max_density(CP<double> axmax, int d) {
   return m;
 }
 
-template <typename T, int MAXD>
-__global__ __launch_bounds__(512) void k_unweight(SampleArgs<T> a, uint64_t q0, int64_t count,
-                                                  const double* wmax, const double* axmax, int S,
-                                                  uint8_t* accept, double* wts, T* pts) {
-  constexpr int GROUP = sizeof(T) == 4 ? 5 : 2;
+template <typename T, int MAXD, bool SHARE>
+__global__ __launch_bounds__(SHARE ? 512 : 256) void k_unweight(
+    SampleArgs<T> a, uint64_t q0, int64_t count, const double* wmax, const double* axmax, int share,
+    uint8_t* accept, double* wts, T* pts) {
+  constexpr int GROUP = sizeof(T) == 4 ? 5 : SHARE || MAXD > 8 ? 2 : 1;
+  const int S = SHARE ? share : 1;
   extern __shared__ __align__(16) unsigned char uw_lds[];
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int group = wave / S, w = wave % S;  // S wavefronts each
+  const int group = SHARE ? wave / S : wave, w = SHARE ? wave % S : 0;  // S wavefronts each
   // the group's r [S kUwPer][64], then as many G (S = 1 needs none)
   T* sr = reinterpret_cast<T*>(uw_lds) + (size_t)group * 2 * S * kUwPer * 64;
   T* sG = sr + S * kUwPer * 64;
@@ -170,7 +178,9 @@ __global__ __launch_bounds__(512) void k_unweight(SampleArgs<T> a, uint64_t q0, 
   CP<float> hab = cp(a.hab);
   T f = T(0), g = T(0);
   const int items = K + a.n_orphan;
-  for (int i0 = 0; i0 < items; i0 += S * kUwPer) {
+  constexpr bool DIRECT = !SHARE && MAXD <= 4;
+  if constexpr (DIRECT) eval_channels<T, MAXD>(a, a.alpha, c, own, jp, p, f, g, nullptr);
+  for (int i0 = 0; !DIRECT && i0 < items; i0 += S * kUwPer) {
     for (int i = 0; i < kUwPer; ++i) {
       const int s = w * kUwPer + i, cc = i0 + s;
       if (cc >= items) break;
@@ -194,7 +204,7 @@ __global__ __launch_bounds__(512) void k_unweight(SampleArgs<T> a, uint64_t q0, 
       } else {
         rr = peak_r<T, MAXD>(pmap + (size_t)orphans[cc - K] * d, d, p);
       }
-      if (S == 1) {  // uniform
+      if constexpr (!SHARE) {
         if (cc < K) {
           f = fma(chan_at(a, cc)->twin, rr, f);
           g = fma((T)alpha[cc] * G, cnorm[cc] * rr, g);
@@ -206,7 +216,7 @@ __global__ __launch_bounds__(512) void k_unweight(SampleArgs<T> a, uint64_t q0, 
       sr[s * 64 + lane] = rr;
       sG[s * 64 + lane] = G;
     }
-    if (S == 1) continue;
+    if constexpr (!SHARE) continue;
     __syncthreads();
     if (w == 0) {
       const int m = min(items - i0, S * kUwPer);
@@ -439,9 +449,13 @@ void unweight_t(const JobDev& j, uint64_t q0, int64_t count, const double* wmax,
   const int S = std::max(1, std::min(terms, fill));
   const int groups = S < 4 ? 4 / S : 1;  // 192- to 512-thread workgroups
   const size_t lds = S > 1 ? (size_t)groups * 2 * S * kUwPer * 64 * sizeof(T) : 0;
-  hipLaunchKernelGGL((k_unweight<T, MAXD>), dim3((unsigned)((blocks + groups - 1) / groups)),
-                     dim3(64 * S * groups), lds, s, a, q0, count, wmax, j.axmax, S, accept, wts,
-                     reinterpret_cast<T*>(pts));
+  const dim3 grid((unsigned)((blocks + groups - 1) / groups)), block(64 * S * groups);
+  if (S > 1)
+    hipLaunchKernelGGL((k_unweight<T, MAXD, true>), grid, block, lds, s, a, q0, count, wmax,
+                       j.axmax, S, accept, wts, reinterpret_cast<T*>(pts));
+  else
+    hipLaunchKernelGGL((k_unweight<T, MAXD, false>), grid, block, 0, s, a, q0, count, wmax,
+                       j.axmax, 1, accept, wts, reinterpret_cast<T*>(pts));
 }
 template <int MAXD>
 void unweight_f64(const JobDev& j, uint64_t q0, int64_t count, const double* wmax,
