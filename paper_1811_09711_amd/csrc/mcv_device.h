@@ -341,12 +341,19 @@ __device__ inline float m_tan(float x) { return tanf(x); }
 // 1.7e-08; in FP32 with the hardware log2 about 2.5e-7, median 4e-8).  The
 // library function spends about 110 instructions over its three branches.
 // The far tail, y < 7.5e-9 down to the smallest denormal (2 - y = 2): the same
-// structure on 26 < w <= 151 (fp64_fit.py; 2e-9 of the fit, FP32 rounding
-// above it).  In line: a call here, though never taken, made the kernels save
-// their registers around every axis (34 spilled VGPRs at d = 10).
+// structure on 26 < w <= 151 (fp64_fit.py; 2e-9 of the fit).  w and its root
+// carry what their rounding left over, and the centre of t its rest beyond
+// FP32: at most 0.9 ulp (0.27 on average; the library's erfcinvf 2.0 and 0.45,
+// without the leftovers 2.3 and 0.61).  In line: a call here, though never
+// taken, made the kernels save their registers around every axis (34 spilled
+// VGPRs at d = 10).
 __device__ inline float erfcinv_far(float y) {
-  const float w = 63.0f - __builtin_amdgcn_logf(y * 0x1p64f);
-  const float t = (sqrtf(w) - 8.693612621e+00f) * 2.781956039e-01f;
+  const float v = y * 0x1p64f;
+  const float e = (float)(63 - __builtin_amdgcn_frexp_expf(v));
+  const float l = __builtin_amdgcn_logf(__builtin_amdgcn_frexp_mantf(v));
+  const float w = e - l, wl = (e - w) - l;
+  const float s = sqrtf(w), sl = (fmaf(-s, s, w) + wl) * (0.5f / s);
+  const float t = ((s - 8.693612621e+00f) + (sl + 4.3184952e-07f)) * 2.781956039e-01f;
   float P = 1.396802121e-05f;
   P = fmaf(P, t, -3.095602143e-05f);
   P = fmaf(P, t, 3.235408476e-05f);
@@ -358,7 +365,7 @@ __device__ inline float erfcinv_far(float y) {
   P = fmaf(P, t, -4.534591285e-03f);
   P = fmaf(P, t, 3.017693168e+00f);
   P = fmaf(P, t, 7.108942973e+00f);
-  return P;
+  return v == 0.0f ? INFINITY : P;
 }
 
 // CENTRAL: the caller knows that w <= 10.

@@ -1,9 +1,12 @@
-"""The tangent of the channel maps as mcv_device.h has it (compiled for the
-CPU, see test_special_ends.py) against mpmath.  Bound: 1/2 ulp of the final
+"""The tangent of the channel maps and the far tail of the FP32 erfcinv as
+mcv_device.h has them (compiled for the CPU, see test_special_ends.py) against
+mpmath.  Tangent: 1/2 ulp of the final
 sum, and the parts that carry no remainder: the polynomial rests of sine and
 cosine, at most 0.1 and 0.42 of their sums (pi / 4), a rounding and a half each
 of their own unit; 1 ulp in all, and 0.3 on average for rounding errors that
-are independent."""
+are independent.  Far tail: 1/2 ulp of the final
+sum, and t (|t| <= 1, in a term of at most 0.42 of the result) with two
+roundings and the slope with one: 1.2 ulp, 0.4 on average."""
 import mpmath as mp
 import numpy as np
 
@@ -27,3 +30,23 @@ def test_tangent(tmp_path):
     for v in ends:
         assert _ulps(lib.t_tan(float(v)), mp.tan(mp.mpf(float(v)))) < 1.0, v
     assert lib.t_tan(0.0) == 0.0 and lib.t_tan(1e-310) == 1e-310 and np.isnan(lib.t_tan(float("nan")))
+
+
+def test_fp32_far_tail(tmp_path):
+    lib = build(tmp_path)
+    mp.mp.dps = 30
+    rng = np.random.default_rng(7)
+    y = np.exp(rng.uniform(np.log(1e-44), np.log(7.4e-9), 2000)).astype(np.float32)
+    e = []
+    for v in y[y > 0]:
+        m = mp.mpf(float(v))
+        z = mp.sqrt(-mp.log(m))
+        for _ in range(60):  # Halley's rule on erfc(z) = y
+            u = (mp.erfc(z) - m) / (-2 / mp.sqrt(mp.pi) * mp.exp(-z * z))
+            step = u / (1 + z * u)
+            z -= step
+            if abs(step) < mp.mpf(10) ** -25:
+                break
+        e.append(float(abs(mp.mpf(lib.t_far(float(v))) - z) / mp.mpf(float(np.spacing(np.float32(float(z)))))))
+    assert max(e) < 1.2 and np.mean(e) < 0.4
+    assert lib.t_far(0.0) == np.inf and np.isnan(lib.t_far(float("nan")))
