@@ -47,9 +47,19 @@ __device__ inline void set_head(char* rec, int c, int d, uint32_t gmask, uint32_
 // channel's workgroup also writes its twin's factor (the norm of the peak of
 // its shape), its equidistant grid (Sec. 3.2: adaptation starts from
 // equidistant bins; in mixed precision rounded to FP32, which keeps them
-// apart) and its weight, and the first its share of the zeroed history.  One
-// launch; as four, with a thread per channel or axis walking its arrays, the
-// set-up of a 10-axis, 32-channel job took 110 us.
+// apart) and its weight.  The history is cleared by workgroups of its own,
+// kZeroRows rows each: with 65536 rows the one wavefront of a one-channel job
+// took 90 of its creation's 175 us.  One launch; as four, with a thread per
+// channel or axis walking its arrays, the set-up of a 10-axis, 32-channel job
+// took 110 us.
+constexpr int kZeroRows = 512;
+constexpr int kMaxZeroGroups = 1024;
+
+inline int zero_groups(int max_iter) {
+  const int g = max_iter / kZeroRows + (max_iter % kZeroRows ? 1 : 0);
+  return g < kMaxZeroGroups ? g : kMaxZeroGroups;
+}
+
 __device__ inline double axis_product(double first, double factor, bool counts, int d) {
   double norm = first;
   for (int k = 0; k < d; ++k) {
@@ -73,6 +83,12 @@ __device__ inline double peak_norm(const JobDev& j, int i, int lane) {
 
 __global__ __launch_bounds__(64) void k_setup(JobDev j) {
   const int lane = threadIdx.x, d = j.d;
+  if ((int)blockIdx.x >= j.K + j.P) {
+    const int64_t g = (int64_t)blockIdx.x - (j.K + j.P), groups = (int64_t)gridDim.x - (j.K + j.P);
+    for (int64_t q = g * 64 + lane; q < (int64_t)j.max_iter * kHistStride; q += groups * 64)
+      j.history[q] = 0.0;
+    return;
+  }
   if ((int)blockIdx.x >= j.K) {
     const int i = (int)blockIdx.x - j.K;
     if (lane < d) {
@@ -224,8 +240,6 @@ __global__ __launch_bounds__(64) void k_setup(JobDev j) {
     const double e = (double)(q % (n + 1)) / (double)n;
     j.edges[(size_t)c * ne + q] = j.prec == 1 ? (double)(float)e : e;
   }
-  for (int64_t q = (int64_t)c * 64 + lane; q < (int64_t)j.max_iter * kHistStride; q += (int64_t)j.K * 64)
-    j.history[q] = 0.0;
 }
 
 // Channel-mask coefficients (mcv_mask.h): thread (c, f) writes feature f of
@@ -1059,7 +1073,7 @@ void set_extents(JobSet& js) {
 }
 
 void launch_setup(const JobDev& j, hipStream_t s) {
-  hipLaunchKernelGGL(k_setup, dim3(j.K + j.P), dim3(64), 0, s, j);
+  hipLaunchKernelGGL(k_setup, dim3(j.K + j.P + zero_groups(j.max_iter)), dim3(64), 0, s, j);
   if (j.masked) {
     const MaskForm F = mask_form_of(j.d);
     hipLaunchKernelGGL(k_setup_mask, dim3(cdiv(((j.K + 31) & ~31) * 16 * F.steps, 256)), dim3(256),
