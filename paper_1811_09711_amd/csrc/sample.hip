@@ -1,7 +1,7 @@
 // Host side of the sample pass (argument records, launches of the
 // single-job kernels instantiated by single.hip and of the batched queue
-// kernels instantiated by queue.hip), plus the per-call trace and the unweighting trial kernels that share its point
-// evaluation.
+// kernels instantiated by queue.hip), plus the per-call trace and the
+// unweighting trial kernels that share its point evaluation.
 //
 // Brass, Kilian, Reuter, arXiv:1811.09711, Sec. 3.5: for every call r_c of
 // channel c, x_c = G_c^{-1}(r_c) with the VEGAS step map (Sec. 3.2, eq. g(x)),
@@ -12,9 +12,10 @@
 //
 // Work split on the GPU (the paper's OpenMP/MPI split is replaced): the
 // calls of a pass are laid out channel by channel (call i belongs to channel c
-// iff S_c <= i < S_{c+1}); workgroup g of G takes the contiguous range
-// [g N/G, (g+1) N/G) and walks it channel segment by channel segment, so every
-// segment is channel-uniform.  Each segment's sums are reduced in registers,
+// iff S_c <= i < S_{c+1}); work unit g of G is the contiguous range
+// [g N/G, (g+1) N/G), and the workgroups of a persistent grid take one unit
+// after another from a counter.  A unit is walked channel segment by channel
+// segment, so every segment is channel-uniform.  Each segment's sums are reduced in registers,
 // wavefront shuffles and LDS into one partial record at slot g + c (unique,
 // since each new segment increments g or c), its LDS histogram is written to
 // the same slot, and a small kernel reduces the slots in order.
@@ -439,13 +440,13 @@ void unweight_t(const JobDev& j, uint64_t q0, int64_t count, const double* wmax,
                 double* wts, void* pts, hipStream_t s) {
   SampleArgs<T> a = make_args<T>(j, kTagUnweight);
   // Wavefronts per 64 trials: kUwPer terms each at least, and no more than
-  // fill the chip's 1024 SIMDs 4 deep: beyond, making the points S times over
+  // fill the chip's SIMDs (4 per CU) 4 deep: beyond, making the points S times over
   // costs more than the waits it hides (12 channels, d = 4, FP64, 262144
   // trials: 291 us with S = 2, 254 with 1; 64 channels, d = 12, FP32, 65536:
   // 302 us with S = 8, 263 with 4).
   const int64_t blocks = (count + 63) / 64;
   const int terms = (j.K + j.n_orphan + kUwPer - 1) / kUwPer;
-  const int fill = (int)std::min<int64_t>(8, std::max<int64_t>(1, 4096 / blocks));
+  const int fill = (int)std::min<int64_t>(8, std::max<int64_t>(1, 16 * j.n_cu / blocks));
   const int S = std::max(1, std::min(terms, fill));
   const int groups = S < 4 ? 4 / S : 1;  // 192- to 512-thread workgroups
   const size_t lds = S > 1 ? (size_t)groups * 2 * S * kUwPer * 64 * sizeof(T) : 0;

@@ -1,5 +1,5 @@
-// Device code of the sample pass shared by the single-job kernel (sample.hip)
-// and the batched queue kernels (queue_f32.hip, queue_f64.hip): the kernel
+// Device code of the sample pass shared by the single-job kernels (single.hip)
+// and the batched queue kernels (queue.hip): the kernel
 // argument record, the per-call forward map and one work unit of a pass.
 //
 // Brass, Kilian, Reuter, arXiv:1811.09711, Sec. 3.5: for every call r_c of
@@ -594,10 +594,9 @@ __device__ __forceinline__ void masked_terms(const SampleArgs<T>& a, int c, int 
 // also write f, g and w of the calls in the argument record's trace window
 // (the same code path otherwise).  MT > 0: the job's hint cells per axis as
 // a constant (its offsets fold into immediates).  MASK: channels left out
-// by masks (mcv_mask.h).  Every thread of the workgroup
-// calls it
-// with the same unit.  staged: the channel whose own table the workgroup holds
-// in LDS (-1: none, and the sums are not yet cleared).
+// by masks (mcv_mask.h).  Every thread of the workgroup calls it with the same
+// unit.  staged: the channel whose own table the workgroup holds in LDS (-1:
+// none, and the sums are not yet cleared).
 template <typename T, int MAXD, int BLOCK, bool EXACT, bool TB, bool TRACE = false, int RNG = 0,
           int MT = 0, bool LAZY = false, bool MASK = false, bool PAIR = false>
 __device__ __forceinline__ void sample_unit(const SampleArgs<T>& a, int g, int G, uint32_t tag,
@@ -701,8 +700,7 @@ __device__ __forceinline__ void sample_unit(const SampleArgs<T>& a, int g, int G
         if constexpr (MASK)
           masked_terms<T, MAXD, GROUP, EXACT>(a, c, d, M, mshift, queue, p, f, gg);
         else
-          other_terms<T, MAXD, GROUP, EXACT, TB, LAZY, PAIR>(a, c, d, M, mshift,
-                                                                                 p, f, gg);
+          other_terms<T, MAXD, GROUP, EXACT, TB, LAZY, PAIR>(a, c, d, M, mshift, p, f, gg);
       }
       // ---- weights and sums (FP64)
       if (valid) {
@@ -924,7 +922,7 @@ __global__ __launch_bounds__(LB, LB == 256 ? (sizeof(T) == 4 ? 6 : 4) : 1) void 
 // 222, 214 and 247).
 template <typename T>
 struct Tune {
-  static constexpr int BLOCK = 256, PPT = 1;
+  static constexpr int BLOCK = 256;  // one call per thread and round
 };
 template <typename T, int MAXD, bool MASK>
 constexpr int kMinWaves =
@@ -944,10 +942,9 @@ constexpr int kMinWaves =
 template <typename T>
 constexpr bool kLazyWalks = sizeof(T) == 4;
 
-template <typename T, int MAXD, int PPT, int BLOCK, bool EXACT, int RNG = 0, int MT = 0,
+template <typename T, int MAXD, int BLOCK, bool EXACT, int RNG = 0, int MT = 0,
           bool MASK = false, bool TRACE = false>
 __global__ __launch_bounds__(BLOCK, (kMinWaves<T, MAXD, MASK>)) void k_sample(SampleArgs<T> a) {
-  static_assert(PPT == 1, "one call per thread and round");
   extern __shared__ __align__(16) unsigned char smem[];
   __shared__ int next_s;
   const uint32_t tag = TRACE ? a.tag : (uint32_t)cp(a.iter)[0];
@@ -1068,10 +1065,10 @@ inline int units_for(const JobDev& j, int per_round, int64_t n_points, int64_t G
 // Work units and workgroups of k_sample for a pass of n_points.
 template <typename T, int MAXD, bool EXACT, int RNG, int MT, bool MASK, bool TRACE = false>
 Split sample_split_m(const JobDev& j, int64_t n_points) {
-  constexpr int BLOCK = Tune<T>::BLOCK, PPT = Tune<T>::PPT;
+  constexpr int BLOCK = Tune<T>::BLOCK;
   SampleArgs<T> a = make_args<T>(j, 0);
   const int lds = lds_layout<T>(a, BLOCK / 64, 0, MASK);
-  auto kern = k_sample<T, MAXD, PPT, BLOCK, EXACT, RNG, MT, MASK, TRACE>;
+  auto kern = k_sample<T, MAXD, BLOCK, EXACT, RNG, MT, MASK, TRACE>;
   if (lds > 64 * 1024 &&
       hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds) !=
           hipSuccess)
@@ -1082,20 +1079,20 @@ Split sample_split_m(const JobDev& j, int64_t n_points) {
       per_cu < 1)
     return Split{0, 0};
   const int G = per_cu * j.n_cu;
-  Split sp{units_for(j, BLOCK * PPT, n_points, G), G};
+  Split sp{units_for(j, BLOCK, n_points, G), G};
   if (sp.G > sp.U) sp.G = sp.U;
   return sp;
 }
 
 template <typename T, int MAXD, bool EXACT, int RNG, int MT, bool MASK>
 Split launch_sample_m(const JobDev& j, int64_t n_points, hipStream_t s) {
-  constexpr int BLOCK = Tune<T>::BLOCK, PPT = Tune<T>::PPT;
+  constexpr int BLOCK = Tune<T>::BLOCK;
   const Split sp = sample_split_m<T, MAXD, EXACT, RNG, MT, MASK>(j, n_points);
   if (sp.G < 1) return sp;
   SampleArgs<T> a = make_args<T>(j, 0);
   a.units = sp.U;
   const int lds = lds_layout<T>(a, BLOCK / 64, 0, MASK);
-  hipLaunchKernelGGL((k_sample<T, MAXD, PPT, BLOCK, EXACT, RNG, MT, MASK>), dim3(sp.G),
+  hipLaunchKernelGGL((k_sample<T, MAXD, BLOCK, EXACT, RNG, MT, MASK>), dim3(sp.G),
                      dim3(BLOCK), lds, s, a);
   return sp;
 }
@@ -1105,7 +1102,7 @@ Split launch_sample_m(const JobDev& j, int64_t n_points, hipStream_t s) {
 template <typename T, int MAXD, bool EXACT, int RNG, int MT, bool MASK>
 Split launch_sample_trace_m(const JobDev& j, int64_t n_points, uint32_t tag, int64_t first,
                             int64_t count, double* out, hipStream_t s) {
-  constexpr int BLOCK = Tune<T>::BLOCK, PPT = Tune<T>::PPT;
+  constexpr int BLOCK = Tune<T>::BLOCK;
   Split sp = sample_split_m<T, MAXD, EXACT, RNG, MT, MASK, true>(j, n_points);
   if (sp.G < 1) return sp;
   SampleArgs<T> a = make_args<T>(j, tag);
@@ -1117,7 +1114,7 @@ Split launch_sample_trace_m(const JobDev& j, int64_t n_points, uint32_t tag, int
   a.tr_count = count;
   a.tr_out = out;
   const int lds = lds_layout<T>(a, BLOCK / 64, 0, MASK);
-  hipLaunchKernelGGL((k_sample<T, MAXD, PPT, BLOCK, EXACT, RNG, MT, MASK, true>), dim3(sp.G),
+  hipLaunchKernelGGL((k_sample<T, MAXD, BLOCK, EXACT, RNG, MT, MASK, true>), dim3(sp.G),
                      dim3(BLOCK), lds, s, a);
   return sp;
 }
