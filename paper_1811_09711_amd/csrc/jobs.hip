@@ -117,13 +117,20 @@ void carve_state(JobDev& j, Carve& c) {
 }
 
 // Whether a job's passes leave channels out by masks and put sparse lookups
-// off (mcv_mask.h, sample_kernel.h): in FP32 from four axes and four channels
-// that the mask can bound on.  Below that the channels' peaks overlap and few
-// are left out (24 channels: d = 2 273 us a pass with them, 227 without; d = 3
-// the same; d = 7 405 and 412, d = 10 840 and 1010, d = 12 290 and 380); in
-// FP64 the 3-axis partial exponent does as well and the queue costs more
-// registers than it saves (d = 10: 2.28 ms with masks, 1.96 without).  Their
-// lookup queues have to fit the LDS besides what the pass needs.
+// off (mcv_mask.h, sample_kernel.h): in FP32 from four axes, with four channels
+// and three quarters of all that the mask can bound on; seven eighths below
+// seven axes.  Below four the channels' peaks overlap and few are left out (24
+// channels: d = 2 273 us a pass with masks, 227 without; d = 3 the same).  A
+// channel that no mask bounds goes through the queue with all its lanes, which
+// costs more than its lookups at once: with a quarter of 48 channels Gaussian
+// and the others Breit-Wigner on two axes a pass with masks takes 1.9 (d = 4),
+// 1.7 (7) and 1.4 (10) times as long as without, with three quarters 1.3, 1.13
+// and 1.03, with seven eighths 1.09, 0.92 and 0.86; with Breit-Wigner widths of
+// 1e-3 and three quarters of 32 Gaussian 1.2 (d = 4 and 5), 0.90 (7 and 8) and
+// 0.81 (10), with all Gaussian 0.94, 0.79 and 0.74.  In FP64 the 3-axis partial
+// exponent does as well and the queue costs more registers than it saves (d =
+// 10: 2.28 ms with masks, 1.96 without).  The lookup queues have to fit the LDS
+// besides what the pass needs.
 bool wants_masks(const mcv_problem* p, JobDev j) {
   if (p->precision != MCV_FP32_MIXED || p->dim < 4) return false;
   const MaskForm f = mask_form_of(p->dim);
@@ -135,7 +142,7 @@ bool wants_masks(const mcv_problem* p, JobDev j) {
     for (int k = 0; k < p->dim; ++k) g += p->chan_kind[(size_t)c * p->dim + k] == MCV_GAUSS;
     ng += f.axes > 0 ? g > 0 : g == p->dim;
   }
-  return ng >= 4;
+  return ng >= 4 && (p->dim < 7 ? 8 * ng >= 7 * p->n_channels : 4 * ng >= 3 * p->n_channels);
 }
 
 // MRG32k3a jump tables and stream starts (layout: JobDev::mrg), from the

@@ -1,9 +1,9 @@
 """The FP32 pass with channel masks (mcv_mask.h, PendingTerms) against the pass
 without, bit for bit.  A job of four channels, three of them Gaussian, has no
-masks; a fifth channel, a narrow Gaussian in a corner that takes half of the
-calls, gives the same job masks.  The first four channels then make the same
-calls with half the weights, and on calls away from the corner the fifth one's
-density kernel is exactly 0: f is the same, g is halved exactly and w doubled.
+masks; four more channels, narrow Gaussians in a corner that take half of the
+calls, give the same job masks.  The first four channels then make the same
+calls with half the weights, and on calls away from the corner the others'
+density kernels are exactly 0: f is the same, g is halved exactly and w doubled.
 The Gaussians overlap, so that a channel wrongly left out shows: dimensions at
 and below the kernels' buckets, in both forms of the mask."""
 import math
@@ -22,9 +22,9 @@ CORNER, NARROW = 0.97, 2e-3
 
 def _problems(d, sigma, seed, shape):
     rng = np.random.default_rng(seed)
-    kind = np.full((5, d), W.GAUSS, np.int32)
-    loc = np.full((5, d), CORNER)
-    width = np.full((5, d), NARROW)
+    kind = np.full((8, d), W.GAUSS, np.int32)
+    loc = np.full((8, d), CORNER)
+    width = np.full((8, d), NARROW)
     loc[0] = rng.uniform(0.3, 0.5, d)
     for c in (1, 2):
         loc[c] = loc[0] + rng.uniform(-1, 1, d) * sigma / math.sqrt(d)
@@ -63,10 +63,10 @@ def test_masks_leave_every_bit(d, shape, sigma, rng):
     a, b = mcv().Integrator(pa), mcv().Integrator(pb)
     for grids in ("flat", "random"):
         if grids == "random":
-            e = random_edges(np.random.default_rng(d), 5, d, 20, fp32=True, spread=1.0)
+            e = random_edges(np.random.default_rng(d), 8, d, 20, fp32=True, spread=1.0)
             a.set_state_for_test(e[:4], None)
             b.set_state_for_test(e, None)
-        b.set_state_for_test(None, np.array([0.125] * 4 + [0.5]))
+        b.set_state_for_test(None, np.full(8, 0.125))
         ta, tb = a.sample_trace(N, 3, 0, N), b.sample_trace(2 * N, 3, 0, N)
         point = a.trace(N, 3, 0, N)
         away = np.max(np.abs(point["p"] - CORNER), axis=1) > 40 * NARROW
