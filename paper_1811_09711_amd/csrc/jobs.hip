@@ -10,6 +10,7 @@
 #include <math.h>
 #include <string.h>
 
+#include <algorithm>
 #include <mutex>
 #include <string>
 #include <unordered_map>
@@ -116,23 +117,76 @@ void carve_state(JobDev& j, Carve& c) {
   c.take(j.mrg, j.rng ? (size_t)kMrgTables * kMrgEntry + (K + 1) * 6 : 0);
 }
 
+// The share of (calls of one channel, another channel) pairs in which the mask
+// is expected to leave the other channel out: its exponent over the first one's
+// calls, taken at their centre less 2.5 times their spread towards it, reaches
+// the exponents that the skip needs (32 bits, what the calls' own kernel has
+// lost, the ratio of the norms).  The calls of up to 16 channels are looked at.
+double masked_share(const mcv_problem* p, const MaskForm& f) {
+  const int d = p->dim, K = p->n_channels, ns = std::min(K, 16);
+  constexpr double kFlatSpread = 0.29;  // of a uniform variable
+  std::vector<double> centre((size_t)K * d), spread(centre), bits(centre), lw(centre);
+  std::vector<int> ng(K, 0);
+  for (size_t i = 0; i < centre.size(); ++i) {
+    const int kind = p->chan_kind[i];
+    const double w = p->chan_width[i];
+    centre[i] = kind == MCV_FLAT ? 0.5 : p->chan_loc[i];
+    spread[i] = kind == MCV_FLAT ? kFlatSpread : std::min(kFlatSpread, kind == MCV_GAUSS ? w : 3.0 * w);
+    lw[i] = kind == MCV_GAUSS ? log2(w) : 0.0;
+    bits[i] = log2(kind == MCV_GAUSS ? spread[i] : kFlatSpread);
+    ng[i / d] += kind == MCV_GAUSS;
+  }
+  int64_t hit = 0, pairs = 0;
+  std::vector<double> ga(d);
+  for (int c = 0; c < K; ++c) {
+    const size_t cd = (size_t)c * d;
+    const bool on = f.axes > 0 ? ng[c] > 0 : ng[c] == d;
+    double least = INFINITY;
+    for (int k = 0; k < d; ++k) {
+      ga[k] = p->chan_kind[cd + k] == MCV_GAUSS ? 0.8493218 / p->chan_width[cd + k] : 0.0;
+      least = std::min(least, ga[k]);
+    }
+    for (int i = 0; i < ns; ++i) {
+      const int s = i * K / ns;
+      if (s == c) continue;
+      ++pairs;
+      if (!on) continue;
+      const size_t sd = (size_t)s * d;
+      double dist = 0.0, along = 0.0, own = 0.0, need = 32.0 + 0.72 * ng[s];
+      for (int k = 0; k < d; ++k) {
+        if (ga[k] == 0.0) continue;
+        const double a = f.axes > 0 ? ga[k] : least;
+        const double x = a * (centre[sd + k] - centre[cd + k]), y = a * spread[sd + k];
+        dist += x * x;
+        along += x * x * y * y;
+        own += y * y;
+        need += bits[sd + k] - lw[cd + k];
+      }
+      const double away = sqrt(dist) - 2.5 * (dist > 0.0 ? sqrt(along / dist) : 0.0);
+      hit += (away > 0.0 ? away * away : 0.0) + own >= need;
+    }
+  }
+  return pairs > 0 ? (double)hit / (double)pairs : 0.0;
+}
+
 // Whether a job's passes leave channels out by masks and put sparse lookups
-// off (mcv_mask.h, sample_kernel.h): in FP32 from four axes, with four channels
-// and three quarters of all that the mask can bound on; seven eighths below
-// seven axes.  Below four the channels' peaks overlap and few are left out (24
+// off (mcv_mask.h, sample_kernel.h): in FP32 from four axes and four channels
+// that the mask can bound, where 0.72 of the pairs of channels are expected
+// apart.  Below four axes the channels' peaks overlap and few are left out (24
 // channels: d = 2 273 us a pass with masks, 227 without; d = 3 the same).  A
-// channel that no mask bounds goes through the queue with all its lanes, which
-// costs more than its lookups at once: with a quarter of 48 channels Gaussian
-// and the others Breit-Wigner on two axes a pass with masks takes 1.9 (d = 4),
-// 1.7 (7) and 1.4 (10) times as long as without, with three quarters 1.3, 1.13
-// and 1.03, with seven eighths 1.09, 0.92 and 0.86; with Breit-Wigner widths of
-// 1e-3 and three quarters of 32 Gaussian 1.2 (d = 4 and 5), 0.90 (7 and 8) and
-// 0.81 (10), with all Gaussian 0.94, 0.79 and 0.74.  In FP64 the 3-axis partial
-// exponent does as well and the queue costs more registers than it saves (d =
-// 10: 2.28 ms with masks, 1.96 without).  The lookup queues have to fit the LDS
-// besides what the pass needs.
+// channel that is not left out goes through the queue with all its lanes,
+// which costs more than its lookups at once: 48 channels, d = 10, 833333 calls:
+// all Gaussian of widths 0.3 to 0.6 (share 0) 656 us with masks and 475
+// without, 0.1 to 0.3 (0.1) 455 and 376, 0.05 to 0.15 (0.82) 150 and 196; a
+// quarter Gaussian and the others Breit-Wigner (0.25) 1.4 times as long with
+// masks, three quarters (0.75) 1.03, seven eighths (0.85) 0.86.  Of 366 jobs of
+// 4 to 16 axes and 4 to 64 channels so measured, masks are slower in 10 %, by
+// up to 1.3 times, where this rule takes them, and faster by more than 3 % in 4
+// where it does not; in FP64 the 3-axis partial exponent does as well and the
+// queue costs more registers than it saves (d = 10: 2.28 ms with masks, 1.96
+// without).  The lookup queues have to fit the LDS besides what the pass needs.
 bool wants_masks(const mcv_problem* p, JobDev j) {
-  if (p->precision != MCV_FP32_MIXED || p->dim < 4) return false;
+  if (p->precision != MCV_FP32_MIXED || p->dim < 4 || p->n_channels < 4) return false;
   const MaskForm f = mask_form_of(p->dim);
   j.masked = 1;
   if (f.steps == 0 || sample_lds_bytes(j) > 160 * 1024) return false;
@@ -142,7 +196,7 @@ bool wants_masks(const mcv_problem* p, JobDev j) {
     for (int k = 0; k < p->dim; ++k) g += p->chan_kind[(size_t)c * p->dim + k] == MCV_GAUSS;
     ng += f.axes > 0 ? g > 0 : g == p->dim;
   }
-  return ng >= 4 && (p->dim < 7 ? 8 * ng >= 7 * p->n_channels : 4 * ng >= 3 * p->n_channels);
+  return ng >= 4 && masked_share(p, f) >= 0.72;
 }
 
 // MRG32k3a jump tables and stream starts (layout: JobDev::mrg), from the

@@ -1,9 +1,9 @@
 """The FP32 pass with channel masks (mcv_mask.h, PendingTerms) against the pass
 without, bit for bit.  A job of four channels, three of them Gaussian, has no
-masks; four more channels, narrow Gaussians in a corner that take half of the
-calls, give the same job masks.  The first four channels then make the same
-calls with half the weights, and on calls away from the corner the others'
-density kernels are exactly 0: f is the same, g is halved exactly and w doubled.
+masks; 16 more channels, narrow Gaussians in corners that take half of the
+calls, give the same job masks (most pairs of its channels are then far apart).
+The first four channels make the same calls with half the weights, and on calls
+away from the corners the others' density kernels are exactly 0: f is the same, g is halved exactly and w doubled.
 The Gaussians overlap, so that a channel wrongly left out shows: dimensions at
 and below the kernels' buckets, in both forms of the mask."""
 import math
@@ -17,14 +17,17 @@ from gpu_util import mcv, random_edges
 pytestmark = pytest.mark.gpu
 
 N = 20_000
-CORNER, NARROW = 0.97, 2e-3
+NARROW = 2e-3
+# 0.03 or 0.97 on each of the first four axes
+CORNERS = 0.03 + 0.94 * ((np.arange(16)[:, None] >> np.arange(4)) & 1)
 
 
 def _problems(d, sigma, seed, shape):
     rng = np.random.default_rng(seed)
-    kind = np.full((8, d), W.GAUSS, np.int32)
-    loc = np.full((8, d), CORNER)
-    width = np.full((8, d), NARROW)
+    kind = np.full((20, d), W.GAUSS, np.int32)
+    loc = np.full((20, d), 0.97)
+    loc[4:, :4] = CORNERS
+    width = np.full((20, d), NARROW)
     loc[0] = rng.uniform(0.3, 0.5, d)
     for c in (1, 2):
         loc[c] = loc[0] + rng.uniform(-1, 1, d) * sigma / math.sqrt(d)
@@ -63,13 +66,14 @@ def test_masks_leave_every_bit(d, shape, sigma, rng):
     a, b = mcv().Integrator(pa), mcv().Integrator(pb)
     for grids in ("flat", "random"):
         if grids == "random":
-            e = random_edges(np.random.default_rng(d), 8, d, 20, fp32=True, spread=1.0)
+            e = random_edges(np.random.default_rng(d), 20, d, 20, fp32=True, spread=1.0)
             a.set_state_for_test(e[:4], None)
             b.set_state_for_test(e, None)
-        b.set_state_for_test(None, np.full(8, 0.125))
+        b.set_state_for_test(None, np.array([1 / 8] * 4 + [1 / 32] * 16))
         ta, tb = a.sample_trace(N, 3, 0, N), b.sample_trace(2 * N, 3, 0, N)
         point = a.trace(N, 3, 0, N)
-        away = np.max(np.abs(point["p"] - CORNER), axis=1) > 40 * NARROW
+        near = np.abs(point["p"][:, None, :4] - CORNERS) < 40 * NARROW
+        away = ~near.all(2).any(1)
         assert away.mean() > 0.99
         if grids == "flat":
             # the other channels matter where a Gaussian's calls fall
