@@ -43,11 +43,11 @@ PEAK_FP64_TFLOPS = 78.6
 KERNEL_SOURCES = ["sample_kernel.h", "single.hip", "mcv_mask.h", "mcv_point.h", "mcv_device.h"]
 # Taken on d=10 / 32 channels / 100 bins, FP32 mode, 1e8 calls per launch
 # (profiles/k_sample_fp32_d10_K32_n100_counters.md).
-COUNTERS = {"sha256": "4ca97510b2b662c2a48476fc2c2f441546e3a438909717e71c4612f3a5ecc4f6",
-            "fetch_kib": 196522.375, "write_kib": 1878388.75,
-            "fetch_factor": 524307.6875 / 1048576.0, "write_factor": 1048576.0 / 1048576.0,
-            "valu_flops_fp32_waves": 1.0555e9, "valu_active": 0.833,
-            "valu_insts_per_cu_cycle": 0.811, "kernel_ms": 4.051}
+COUNTERS = {"sha256": "c282d307f9e3711cb1ea0223c6d17b2e5eb8a34c0479681bcfea8fe5a250590b",
+            "fetch_kib": 197782.40625, "write_kib": 1874970.265625,
+            "fetch_factor": 524315.8125 / 1048576.0, "write_factor": 1048576.0 / 1048576.0,
+            "valu_flops_fp32_waves": 1.0555e+09, "valu_active": 0.833,
+            "valu_insts_per_cu_cycle": 0.811, "kernel_ms": 4.089}
 
 
 def kernel_sources_digest() -> str:

@@ -49,9 +49,10 @@ inline MaskForm mask_form_of(int d) {
   return mask_form(m, d == m);
 }
 
-// The features of one call at p.  An axis beyond d, where p is 0, adds nothing:
-// in the second form its q = -1/2 would enter the sum of squares, which bounds
-// the exponent from below over the d axes alone.
+// The features of one call at p.  In the second form an axis beyond d, where p
+// is 0, must add nothing: its q = -1/2 would enter the sum of squares, which
+// bounds the exponent from below over the d axes alone.  In the first form its
+// coefficients are 0.
 template <int MAXD, bool EXACT, typename T, int N>
 __device__ __forceinline__ void mask_features(const T (&p)[MAXD], int d, float ee, float (&x)[N]) {
   constexpr MaskForm F = mask_form(MAXD, EXACT);
@@ -61,13 +62,14 @@ __device__ __forceinline__ void mask_features(const T (&p)[MAXD], int d, float e
   x[F.e] = ee;
 #pragma unroll
   for (int k = 0; k < MAXD; ++k) {
-    const float q = EXACT || k < d ? (float)p[k] - 0.5f : 0.0f;
+    float q = (float)p[k] - 0.5f;
     if constexpr (F.axes > 0) {
       if (k < F.axes) {
         x[k] = q;
         x[F.q2 + k] = q * q;
       }
     } else {
+      if (!EXACT && k >= d) q = 0.0f;
       x[k] = q;
       x[F.q2] = fmaf(q, q, x[F.q2]);
     }
